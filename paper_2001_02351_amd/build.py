@@ -32,13 +32,19 @@ SOURCES = ["rp_api.cpp", "fft.hip", "pair.hip", "tetra.hip", "chi_f64.hip", "chi
            "screen.hip", "wannier.hip", "qsum.hip", "symmetry.hip"]
 
 
+# FP64 matrix-core kernels that fit two or more waves per SIMD: accumulators in
+# ordinary registers (in AGPRs the compiler moves them all once per loop pass)
+VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
+SOURCE_FLAGS = {"chi_f64.hip": VGPR_MFMA}
+
+
 def library_path() -> str:
     return LIB
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(BUILD, os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *SOURCE_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     noise = "is not a recognized feature for this target"
     err = "\n".join(l for l in res.stderr.splitlines() if noise not in l)

@@ -372,6 +372,10 @@ static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, con
 
 // ---- steps a5-a6: validated weight and contraction work -------------------
 
+// Most bytes of partial chi that a sliced FP64 contraction may take (slices
+// matter where chi is small: 16 slices of 20 frequencies at N_G = 200 are 205 MB).
+constexpr size_t kF64PartMax = (size_t)256 << 20;
+
 struct ChiJob {
     Geometry g;
     int nband = 0;
@@ -385,6 +389,7 @@ struct ChiJob {
     rp_precision prec = RP_FP64;
     bool herm = false;  // real weights: chi Hermitian
     Tune tune;          // contraction launch shape
+    size_t part_max = kF64PartMax;  // bound on the FP64 contraction's partial chi
 };
 
 static rp_status weights_check(rp_ctx *ctx, const double *E, int nfreq, const double *freq_eV, double delta_eV,
@@ -446,7 +451,9 @@ static ChiBytes chi_bytes(const ChiJob &c, long npair)
 {
     ChiBytes b;
     b.w = sizeof(double2) * (size_t)std::max(1L, npair) * c.nfreq;
-    if (c.prec != RP_FP64) {
+    if (c.prec == RP_FP64) {
+        b.part = chi_f64_part_bytes(npair, c.ng, c.nfreq, c.herm, c.part_max);
+    } else {
         b.a = split_a_bytes(npair, c.ng);
         b.b = split_b_bytes(npair, c.ng);
         b.sw = split_w_bytes(npair, c.nfreq);
@@ -482,7 +489,7 @@ static rp_status chi_enqueue(rp_ctx *ctx, const ChiJob &c, int k0, int k1, const
     }
     if (c.prec == RP_FP64) {
         StageTimer t(ctx, RP_STAGE_CHI);
-        launch_chi_f64(ctx->stream, npair, c.ng, M, c.nfreq, bufs.w, accumulate, c.herm, chi);
+        launch_chi_f64(ctx->stream, npair, c.ng, M, c.nfreq, bufs.w, accumulate, c.herm, c.part_max, bufs.part, chi);
     } else {
         const int nterm = c.prec == RP_SPLIT_BF16 ? 2 : 3;
         {
@@ -733,8 +740,8 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
         if ((st = ensure(ctx, ctx->split_a, nb.a)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
-        if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
     }
+    if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, freq_eV, sizeof(double2) * nfreq)) != RP_OK) return st;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
                        ctx->chi_part.p};
@@ -759,8 +766,11 @@ rp_status rp_chi0_accumulate_noalloc(rp_ctx *ctx, const rp_cell *cell, const int
     // the workspace of rp_chi0_accumulate, carved from the fixed array in
     // 256-byte aligned pieces: frequencies, weights, split operands, partial tiles
     const long npair = (long)(k1 - k0) * (e1 - e0) * (o1 - o0);
-    const ChiBytes nb = chi_bytes(c, npair);
     auto up = [](size_t n) { return (n + 255) / 256 * 256; };
+    // an FP64 contraction cuts fewer slices where the rest of the array is small
+    const size_t fixed = up(sizeof(double2) * nfreq) + up(sizeof(double2) * (size_t)std::max(1L, npair) * nfreq);
+    c.part_max = std::min(kF64PartMax, fixed < kScratchBytes ? kScratchBytes - fixed : 0);
+    const ChiBytes nb = chi_bytes(c, npair);
     const size_t off_f = 0, off_w = up(sizeof(double2) * nfreq);
     const size_t off_a = off_w + up(nb.w), off_b = off_a + up(nb.a), off_sw = off_b + up(nb.b);
     const size_t off_part = off_sw + up(nb.sw), need = off_part + up(nb.part);
@@ -847,8 +857,8 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
         if ((st = ensure(ctx, ctx->split_a, nb.a)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
-        if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
     }
+    if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->glist, p->gsph, sizeof(int) * 3 * p->ng)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, p->freq_eV, sizeof(double2) * p->nfreq)) != RP_OK) return st;
     const int *dg = (const int *)ctx->glist.p;
@@ -926,8 +936,8 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         if ((st = ensure(ctx, ctx->split_a, cb.a)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_b, cb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, cb.sw)) != RP_OK) return st;
-        if ((st = ensure(ctx, ctx->chi_part, cb.part)) != RP_OK) return st;
     }
+    if ((st = ensure(ctx, ctx->chi_part, cb.part)) != RP_OK) return st;
     // host staging of every G list and frequency list, one copy to the device
     std::vector<char> stage(stage_b, 0);
     for (int i = 0; i < nprob; i++) {

@@ -171,9 +171,12 @@ void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nban
                     int mode, double ef_eV, double2 *w);
 
 // chi_f64.hip: chi += sum_p w_p M_p M_p^H on FP64 matrix cores.  herm: the
-// weights are real and only the upper tiles are formed (chi Hermitian).
-void launch_chi_f64(hipStream_t s, long npair, int ng, const double2 *M, int nfreq,
-                    const double2 *w, int accumulate, bool herm, double2 *chi);
+// weights are real and only the upper tiles are formed (chi Hermitian).  Few
+// tiles are cut into slices of the pairs; part holds their partial chi,
+// chi_f64_part_bytes of it, never more than part_max (the same in both calls).
+size_t chi_f64_part_bytes(long npair, int ng, int nfreq, bool herm, size_t part_max);
+void launch_chi_f64(hipStream_t s, long npair, int ng, const double2 *M, int nfreq, const double2 *w,
+                    int accumulate, bool herm, size_t part_max, void *part, double2 *chi);
 
 // chi_bf16.hip: split-BF16 contraction (herm as above; part holds the
 // partial tiles when the pair steps are sliced, chi_part_bytes of them).
