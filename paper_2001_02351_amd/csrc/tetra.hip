@@ -102,7 +102,7 @@ __device__ __forceinline__ double2 crecip(double2 w)
 
 // Series coefficients 6 / (m (m-1) (m-2) (m-3)) of the m-th Taylor term,
 // m = 4 .. kSeriesMax - 1 (the m-th entry; entries below 4 unused).
-constexpr int kSeriesMax = 4 + 96;
+constexpr int kSeriesMax = 4 + 96;   // a multiple of the four terms summed at a time
 struct SeriesTable {
     double f[kSeriesMax];
 };
@@ -152,24 +152,29 @@ __device__ __forceinline__ double2 dd_series(double2 z, const double *x, int a, 
     }
     double2 wp = make_double2(1.0, 0.0);  // w^-(m-3)
     int quiet = 0;
-    for (int m = 4; m < kSeriesMax; m++) {
-        if (m > N) {
-            // raise P to degree m - N: h_k(y_0..y_i) = h_k(y_0..y_{i-1}) + y_i h_{k-1}(y_0..y_i)
-            P[0] *= y[0];
+    // four terms at a time, so that their table entries are fetched together
+    // (one fetch per term kept the loop waiting); the terms after the last are
+    // not added
+    for (int mb = 4; mb < kSeriesMax && quiet < 2; mb += 4) {
 #pragma unroll
-            for (int i = 1; i <= N; i++) P[i] = P[i - 1] + y[i] * P[i];
-        }
-        wp = cmul(wp, wi);
-        const double fh = c_series.f[m] * P[N];
-        const double2 t = make_double2(wp.x * fh, wp.y * fh);
-        sum = cadd(sum, t);
-        // stop after two consecutive terms below 1e-17 of the sum: the terms
-        // shrink at least fourfold, and FP64 resolves 1.1e-16 of the sum
-        const double tm = fabs(t.x) + fabs(t.y), sm = fabs(sum.x) + fabs(sum.y);
-        if (tm <= 1e-17 * sm) {
-            if (++quiet == 2) break;
-        } else {
-            quiet = 0;
+        for (int i4 = 0; i4 < 4; i4++) {
+            if (i4 > 0 || mb > 4 || N < 4) {
+                // raise P to degree m - N: h_k(y_0..y_i) = h_k(y_0..y_{i-1}) + y_i h_{k-1}(y_0..y_i)
+                P[0] *= y[0];
+#pragma unroll
+                for (int i = 1; i <= N; i++) P[i] = P[i - 1] + y[i] * P[i];
+            }
+            wp = cmul(wp, wi);
+            const double fh = c_series.f[mb + i4] * P[N];
+            const double2 t = make_double2(wp.x * fh, wp.y * fh);
+            const double2 next = cadd(sum, t);
+            // stop after two consecutive terms below 1e-17 of the sum: the terms
+            // shrink at least fourfold, and FP64 resolves 1.1e-16 of the sum
+            const bool more = quiet < 2;
+            sum.x = more ? next.x : sum.x;
+            sum.y = more ? next.y : sum.y;
+            const bool small = fabs(t.x) + fabs(t.y) <= 1e-17 * (fabs(sum.x) + fabs(sum.y));
+            quiet = more ? (small ? quiet + 1 : 0) : quiet;
         }
     }
     return sum;
@@ -320,41 +325,34 @@ __device__ __forceinline__ void sort5(double (&xs)[5], double2 (&ls)[5])
 #undef RP_CSWAP
 }
 
-// (1/|T|) int over {E_b < E_F < E_a} within T of lambda_v / (z - e): the
-// region is tiled by clipping T first to E_b < E_F, then each piece to
-// E_a > E_F; a piece S contributes (|S|/|T|) sum_j lambda_v(s_j) I_j^S(z),
-// I_j^S the vertex integral of S on the transition energies at its corners
-// (lambda_v is linear, so it is the barycentric combination of its corner
-// values).
-__device__ double2 clipped_vertex_integral(double2 zz, const double (&e)[4], const double (&eb)[4],
-                                           const double (&ea)[4], double ef, int v)
+// The part {E_b < E_F < E_a} of a tetrahedron T: T is clipped to E_b < E_F,
+// then each piece to E_a > E_F.  A piece S contributes
+// (|S|/|T|) sum_j lambda_v(s_j) I_j^S, I_j^S the vertex integral of S on the
+// transition energies at its corners (lambda_v is linear, so it is the
+// barycentric combination of its corner values).  The pieces, as their corner
+// energies and the factors (|S|/|T|) lambda_v(s_j), are appended to (pc, n).
+constexpr int kMaxPieces = 9;   // three of the first cut, three of each by the second
+struct Piece {
+    double e[4], lam[4];
+};
+
+__device__ void clipped_pieces(const double (&e)[4], const double (&eb)[4], const double (&ea)[4], double ef, int v,
+                               Piece *pc, int &n)
 {
     const double T[4][4] = {{1, 0, 0, 0}, {0, 1, 0, 0}, {0, 0, 1, 0}, {0, 0, 0, 1}};
     double phi1[4];
 #pragma unroll
     for (int c = 0; c < 4; c++) phi1[c] = eb[c] - ef;
-    double2 acc = make_double2(0.0, 0.0);
     auto inner = [&](const double (&r0)[4], const double (&r1)[4], const double (&r2)[4], const double (&r3)[4]) {
         const double ratio = fabs(det4(r0, r1, r2, r3));
         if (!(ratio > 0.0)) return;
         const double *R[4] = {r0, r1, r2, r3};
-        double eS[4];
-        double2 lS[4];
 #pragma unroll
         for (int j = 0; j < 4; j++) {
-            eS[j] = R[j][0] * e[0] + R[j][1] * e[1] + R[j][2] * e[2] + R[j][3] * e[3];
-            lS[j] = clog_d(make_double2(zz.x - eS[j], zz.y));
+            pc[n].e[j] = R[j][0] * e[0] + R[j][1] * e[1] + R[j][2] * e[2] + R[j][3] * e[3];
+            pc[n].lam[j] = ratio * R[j][v];
         }
-        for (int j = 0; j < 4; j++) {
-            const double lam = R[j][v];
-            if (lam == 0.0) continue;
-            double xs[5] = {eS[0], eS[1], eS[2], eS[3], eS[j]};
-            double2 ls[5] = {lS[0], lS[1], lS[2], lS[3], lS[j]};
-            sort5(xs, ls);
-            const double2 d = dd4_sorted(zz, xs, ls);
-            acc.x += ratio * lam * d.x;
-            acc.y += ratio * lam * d.y;
-        }
+        n++;
     };
     auto outer = [&](const double (&q0)[4], const double (&q1)[4], const double (&q2)[4], const double (&q3)[4]) {
         const double Q[4][4] = {{q0[0], q0[1], q0[2], q0[3]}, {q1[0], q1[1], q1[2], q1[3]},
@@ -366,36 +364,428 @@ __device__ double2 clipped_vertex_integral(double2 zz, const double (&e)[4], con
         clip_tet(Q, phi2, inner);
     };
     clip_tet(T, phi1, outer);
-    return acc;
 }
 
-constexpr int kWThreads = 128;
+constexpr int kWThreads = 256;
+constexpr int kWPairs = 32;                       // pairs per workgroup
+constexpr int kWLanes = kWThreads / kWPairs;      // threads per pair
+constexpr int kWTets = 24 / kWLanes;              // tetrahedra per thread
+constexpr int kWFreqs = 2 * kWLanes;              // frequencies per pass over the pairs
+constexpr int kWMinFreqs = 2;                     // fewest frequencies per workgroup
+constexpr int kMoments = 72;                      // 0.6^72 = 1.1e-16
+constexpr double kSeriesRatio = 0.6;
+static_assert(kWLanes == 8 && kWTets == 3, "eight threads per pair, three tetrahedra each");
 
-// One thread per (pair, frequency).  The corner energies e_j of the 15
-// distinct corners live in registers (the tetrahedron table indexes them with
-// the same slot in every lane, which the compiler turns into register-relative
-// moves) and the logarithms log(z - e_j) in LDS ([slot][thread]), so five
-// 128-thread blocks share a CU; each of the 24 tetrahedra sorts its five nodes
-// (four corners, k's corner doubled) together with their logarithms and
-// evaluates I_v(z) and I_v(z') (only I_v(z) when z' = z*).
+template <int CTRL> __device__ __forceinline__ double dpp(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+
+// sum over the eight threads of a pair, in a fixed order (quad_perm over
+// lanes s ^ 1 and s ^ 2, then the mirrored half row: the quads hold equal sums)
+__device__ __forceinline__ double sum8(double v)
+{
+    v += dpp<0xB1>(v);
+    v += dpp<0x4E>(v);
+    v += dpp<0x141>(v);
+    return v;
+}
+
+// One workgroup per 32 pairs and a range of frequencies.
+//
+// All 24 tetrahedra of a pair together: with c the middle of the 15 corner
+// energies, R half their spread and y = (e - c)/R,
+//     sum_T I_v(z) = sum_m mu_m R^m / (z - c)^(m+1),   mu_m = sum_T <lambda_v y^m>_T
+//     <lambda_v y^m>_T = 6 m!/(m+4)! h_m(y_0, .., y_3, y_v)
+// (h_m the complete homogeneous symmetric polynomial; Hermite-Genocchi).  The
+// moments mu_m do not depend on the frequency: eight threads per pair form 72
+// of them from three tetrahedra each, and every frequency with
+// R <= 0.6 |z - c| is one Horner sum of them to 1e-16.  Frequencies nearer to
+// the pair's energies (9% of those of the 48^3 workload's z and z', none on
+// the imaginary axis) go to a list, and one thread per (entry,
+// tetrahedron) evaluates the divided difference from the entry's 15 logarithms
+// log(z - e_j) in LDS.  No sum depends on which entries share a workgroup.
+//
+// The work is FP64 vector arithmetic and its latency.  With one thread per
+// (pair, frequency) evaluating all 24 tetrahedra, 46% of the lanes active, the
+// weights of 128 000 pairs x 20 real frequencies (48^3 workload) took 6.39 ms,
+// now 1.70; 16 imaginary frequencies 1.33 ms, now 0.19; a metal's 14 112 pairs
+// x 10 frequencies 7.45 ms, now 0.99; 3 072 pairs x 10 0.76 ms, now 0.20.
 //
 // METAL: the Fermi level ef (hartree) cuts the tetrahedra.  With E_b < ef at
 // all four corners of a tetrahedron and E_a > ef at all four, the insulating
 // integral applies; with E_b >= ef or E_a <= ef at all four, the tetrahedron
-// contributes nothing; otherwise clipped_vertex_integral tiles the part where
-// E_b < ef < E_a (the corner energies of both bands are kept in LDS too).
+// contributes nothing; otherwise its part where E_b < ef < E_a is tiled by
+// smaller tetrahedra (clipped_pieces), whose moments (for all frequencies at
+// once) or integrals replace its own.
 template <bool METAL>
-__global__ void __launch_bounds__(kWThreads)
+__global__ void __launch_bounds__(kWThreads, METAL ? 1 : 2)
 k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T,
-          int o0, int nO, int e0, int nE, int k0, long npair, int nfreq, const double2 *freq,
-          double delta, int mode, double ef, double2 *w)
+          int o0, int nO, int e0, int nE, int k0, long npair, int nfreq, int fper, const double2 *freq,
+          double delta, double ef, double2 *w)
 {
-    double eR[15];
-    __shared__ double2 sL[15][kWThreads];
-    __shared__ double sB[METAL ? 15 : 1][kWThreads];
-    __shared__ double sA[METAL ? 15 : 1][kWThreads];
+    __shared__ double sE[15][kWPairs];
+    __shared__ double sB[METAL ? 15 : 1][kWPairs];
+    __shared__ double sA[METAL ? 15 : 1][kWPairs];
+    __shared__ double sMu[kMoments][kWPairs];
+    __shared__ double sC[kWPairs], sR[kWPairs], sFac[kWPairs];
+    __shared__ double2 sL[kWPairs][15];
+    __shared__ double2 sVal[kWPairs * 24];
+    // entries (frequency, pair, which of z and z'): from the front those of uncut
+    // tetrahedra, from the back (METAL) those of pairs with cut ones
+    __shared__ int sQueue[kWPairs * kWFreqs];
+    __shared__ int sNq, sNcut, sSome[kWPairs];   // sSome: 0 nothing, 1 some, 2 whole tetrahedra only
+    __shared__ Piece sPc[METAL ? 24 * kMaxPieces : 1];
+    __shared__ int sNpc;
+    __shared__ double2 sSum[kWThreads / 64];
     const int tid = threadIdx.x;
-    const long t = (long)blockIdx.x * blockDim.x + tid;
+    const long p0 = (long)blockIdx.x * kWPairs;
+    const int fa = blockIdx.y * fper, fb = min(nfreq, fa + fper);
+    const double ha = 1.0 / kHartreeEv;
+    const double dl = delta * ha;
+    const int lane8 = tid & (kWLanes - 1), slot = tid / kWLanes;
+
+    // corner energies (a pair past the end repeats the last one and is not stored)
+    {
+        const long p = min(p0 + slot, npair - 1);
+        const int b = o0 + (int)(p % nO);
+        const int a = e0 + (int)((p / nO) % nE);
+        const int k = k0 + (int)(p / ((long)nO * nE));
+        const int n1 = k / (K2 * K3), n2 = (k / K3) % K2, n3 = k % K3;
+        for (int j = lane8; j < 15; j += kWLanes) {
+            const int code = c_tetra.nbr[j];
+            const int m1 = n1 + code / 9 - 1, m2 = n2 + (code / 3) % 3 - 1, m3 = n3 + code % 3 - 1;
+            const int kv = (mesh_wrap(m1, K1) * K2 + mesh_wrap(m2, K2)) * K3 + mesh_wrap(m3, K3);
+            const int kvq = (mesh_wrap(m1 + q1, K1) * K2 + mesh_wrap(m2 + q2, K2)) * K3 + mesh_wrap(m3 + q3, K3);
+            const double eb = E[(long)kv * nband + b], ea = E[(long)kvq * nband + a];
+            sE[j][slot] = (ea - eb) * ha;
+            if constexpr (METAL) {
+                sB[j][slot] = eb * ha;
+                sA[j][slot] = ea * ha;
+            }
+        }
+        if (lane8 == 0) {
+            double fac = 2.0 / (double)(K1 * K2 * K3);
+            if (T) {
+                const int kq = (mesh_wrap(n1 + q1, K1) * K2 + mesh_wrap(n2 + q2, K2)) * K3 + mesh_wrap(n3 + q3, K3);
+                fac *= 1.0 - T[(long)kq * nband + a] * T[(long)k * nband + b];
+            }
+            sFac[slot] = fac;
+        }
+    }
+    __syncthreads();
+    // moments: thread (slot, lane8) takes tetrahedra 3 lane8 .. 3 lane8 + 2
+    {
+        double lo = sE[0][slot], hi = lo;
+#pragma unroll
+        for (int j = 1; j < 15; j++) {
+            lo = fmin(lo, sE[j][slot]);
+            hi = fmax(hi, sE[j][slot]);
+        }
+        const double c = 0.5 * (lo + hi), R = 0.5 * (hi - lo), ri = R > 0.0 ? 1.0 / R : 0.0;
+        if (lane8 == 0) {
+            sC[slot] = c;
+            sR[slot] = R;
+        }
+        bool whole = true, some = true;   // every tetrahedron uncut / any of them contributes
+        int kind[kWTets];                 // METAL: 0 nothing, 1 uncut, 2 cut
+        if constexpr (METAL) {
+            some = false;
+#pragma unroll
+            for (int i = 0; i < kWTets; i++) {
+                bool all_in = true, none_b = true, none_a = true;
+#pragma unroll
+                for (int v = 0; v < 4; v++) {
+                    const int sl = c_tetra.slot[kWTets * lane8 + i][v];
+                    const double bb = sB[sl][slot], aa = sA[sl][slot];
+                    all_in = all_in && bb < ef && aa > ef;
+                    none_b = none_b && !(bb < ef);
+                    none_a = none_a && !(aa > ef);
+                }
+                kind[i] = none_b || none_a ? 0 : all_in ? 1 : 2;
+                whole = whole && kind[i] == 1;
+                some = some || kind[i] != 0;
+            }
+            const unsigned long long group = 0xffull << (tid & 63 & ~(kWLanes - 1));
+            whole = (__ballot(whole) & group) == group;
+            some = (__ballot(some) & group) != 0;
+        }
+        if (lane8 == 0) sSome[slot] = whole ? 2 : some;
+        if (whole) {
+            double y[kWTets][5], P[kWTets][5];
+#pragma unroll
+            for (int i = 0; i < kWTets; i++)
+#pragma unroll
+                for (int v = 0; v < 5; v++) {
+                    const int sl = v < 4 ? c_tetra.slot[kWTets * lane8 + i][v] : kTet.self;
+                    y[i][v] = (sE[sl][slot] - c) * ri;
+                    P[i][v] = 1.0;
+                }
+            for (int m = 0; m < kMoments; m++) {
+                double h = 0.0;
+#pragma unroll
+                for (int i = 0; i < kWTets; i++) {
+                    h += P[i][4];
+                    // raise to degree m + 1: h_k(y_0..y_v) = h_k(y_0..y_{v-1}) + y_v h_{k-1}(y_0..y_v)
+                    P[i][0] *= y[i][0];
+#pragma unroll
+                    for (int v = 1; v < 5; v++) P[i][v] = P[i][v - 1] + y[i][v] * P[i][v];
+                }
+                h = sum8(h);
+                if (lane8 == 0) sMu[m][slot] = c_series.f[m + 4] * h;
+            }
+        } else if constexpr (METAL) {
+            if (some) {
+                Piece pc[kMaxPieces];
+                double mu[kMoments];
+#pragma unroll
+                for (int m = 0; m < kMoments; m++) mu[m] = 0.0;
+                for (int i = 0; i < kWTets; i++) {
+                    double e4[4], b4[4], a4[4];
+                    int iv = 0, n = 0;
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        const int sl = c_tetra.slot[kWTets * lane8 + i][v];
+                        e4[v] = sE[sl][slot];
+                        b4[v] = sB[sl][slot];
+                        a4[v] = sA[sl][slot];
+                        if (sl == kTet.self) iv = v;
+                    }
+                    if (kind[i] == 1) {
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            pc[0].e[v] = e4[v];
+                            pc[0].lam[v] = v == iv ? 1.0 : 0.0;
+                        }
+                        n = 1;
+                    } else if (kind[i] == 2) {
+                        clipped_pieces(e4, b4, a4, ef, iv, pc, n);
+                    }
+                    for (int q = 0; q < n; q++) {
+                        // sum_j lam_j h_m(s_0..s_3, s_j) with h_m(.., s_j) = h_m(s_0..s_3) + s_j h_{m-1}(.., s_j)
+                        double y[4], P[4], H[4], lam[4];
+#pragma unroll
+                        for (int j = 0; j < 4; j++) {
+                            y[j] = (pc[q].e[j] - c) * ri;
+                            lam[j] = pc[q].lam[j];
+                            P[j] = 1.0;
+                            H[j] = 0.0;
+                        }
+#pragma unroll
+                        for (int m = 0; m < kMoments; m++) {
+#pragma unroll
+                            for (int j = 0; j < 4; j++) {
+                                H[j] = P[3] + y[j] * H[j];
+                                mu[m] += lam[j] * H[j];
+                            }
+                            P[0] *= y[0];
+#pragma unroll
+                            for (int j = 1; j < 4; j++) P[j] = P[j - 1] + y[j] * P[j];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < kMoments; m++) {
+                    const double h = sum8(mu[m]);
+                    if (lane8 == 0) sMu[m][slot] = c_series.f[m + 4] * h;
+                }
+            }
+        }
+    }
+    __syncthreads();
+    for (int fc = fa; fc < fb; fc += kWFreqs) {
+        if (tid == 0) sNq = sNcut = 0;
+        __syncthreads();
+        // the series: thread (pair, frequency)
+        const int pr = tid & (kWPairs - 1);
+        const long p = p0 + pr;
+        const double c = sC[pr], R = sR[pr];
+        for (int f = fc + tid / kWPairs; f < min(fb, fc + kWFreqs); f += kWLanes) {
+            const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
+            // on the imaginary axis without broadening z' = z*, and since the
+            // corner energies are real I_v(z*) = conj(I_v(z)): x = 2 Re sum I_v(z)/6
+            const bool conj_pair = dl == 0.0 && om.x == 0.0;
+            double2 x = make_double2(0.0, 0.0);
+            int far = 0;   // bit zi: z (0) or z' (1) is left to the exact integrals
+            if (p < npair && sSome[pr]) {
+                for (int zi = 0; zi < (conj_pair ? 1 : 2); zi++) {
+                    const double2 u = zi ? make_double2(-om.x - c, -om.y + dl) : make_double2(om.x - c, om.y + dl);
+                    const double a2 = u.x * u.x + u.y * u.y;
+                    if (!(R * R <= kSeriesRatio * kSeriesRatio * a2)) {
+                        far |= 1 << zi;
+                        continue;
+                    }
+                    const double2 ui = make_double2(u.x / a2, -u.y / a2), r = cscale(ui, R);
+                    // terms until (R/|u|)^n < 1e-16
+                    const float lr = -0.5f * __logf((float)(R * R / a2) + 1e-30f);
+                    const int n = min(kMoments, (int)(36.9f / lr) + 2);
+                    double2 s = make_double2(0.0, 0.0);
+#pragma unroll 4
+                    for (int m = n - 1; m >= 0; m--) {
+                        const double t = s.x * r.x - s.y * r.y + sMu[m][pr];
+                        s.y = s.x * r.y + s.y * r.x;
+                        s.x = t;
+                    }
+                    x = cadd(x, cmul(s, ui));
+                }
+                if (conj_pair) x = make_double2(2.0 * x.x, 0.0);
+            }
+            if (far) {
+                const int at = !METAL || sSome[pr] == 2 ? atomicAdd(&sNq, 1) : kWPairs * kWFreqs - 1 - atomicAdd(&sNcut, 1);
+                sQueue[at] = ((f - fc) * kWPairs + pr) * 4 + far;
+            }
+            if (p < npair) w[(long)f * npair + p] = cscale(x, sFac[pr] * (1.0 / 6.0));
+        }
+        __syncthreads();
+        // the rest, 32 entries at a time: one thread per (entry, tetrahedron),
+        // then one per entry adds its 24 values in order
+        const int nq = sNq;
+        for (int base = 0; base < nq; base += kWPairs) {
+            const int n = min(kWPairs, nq - base);
+            const bool on = slot < n;
+            const int own = on ? sQueue[base + slot] : 0;
+            double2 x = make_double2(0.0, 0.0);
+            for (int zi = 0; zi < 2; zi++) {
+                auto zof = [&](int item) {
+                    const double2 v = freq[fc + (item >> 2) / kWPairs];
+                    const double2 om = make_double2(v.x * ha, v.y * ha);
+                    return zi ? make_double2(-om.x, -om.y + dl) : make_double2(om.x, om.y + dl);
+                };
+                for (int u = tid; u < n * 15; u += kWThreads) {
+                    const int it = u / 15, j = u - it * 15, item = sQueue[base + it];
+                    if (!(item >> zi & 1)) continue;
+                    const double2 zz = zof(item);
+                    sL[it][j] = clog_d(make_double2(zz.x - sE[j][(item >> 2) & (kWPairs - 1)], zz.y));
+                }
+                __syncthreads();
+                for (int u = tid; u < n * 24; u += kWThreads) {
+                    const int it = u / 24, tt = u - it * 24, item = sQueue[base + it];
+                    if (!(item >> zi & 1)) continue;
+                    double xs[5];
+                    double2 ls[5];
+#pragma unroll
+                    for (int v = 0; v < 5; v++) {
+                        const int sl = v < 4 ? c_tetra.slot[tt][v] : kTet.self;
+                        xs[v] = sE[sl][(item >> 2) & (kWPairs - 1)];
+                        ls[v] = sL[it][sl];
+                    }
+                    sort5(xs, ls);
+                    sVal[u] = dd4_sorted(zof(item), xs, ls);
+                }
+                __syncthreads();
+                if (lane8 == 0 && (own >> zi & 1))
+                    for (int i = 0; i < 24; i++) x = cadd(x, sVal[slot * 24 + i]);
+            }
+            if (on && lane8 == 0) {
+                const int pi = (own >> 2) & (kWPairs - 1), f = fc + (own >> 2) / kWPairs;
+                if (dl == 0.0 && freq[f].x == 0.0) x = make_double2(2.0 * x.x, 0.0);   // z' = z*
+                double2 *o = w + (long)f * npair + p0 + pi;
+                *o = cadd(*o, cscale(x, sFac[pi] * (1.0 / 6.0)));
+            }
+            __syncthreads();
+        }
+        // METAL, pairs with cut tetrahedra: the workgroup takes one entry at a
+        // time, 24 threads cut its tetrahedra into pieces and every thread
+        // evaluates some of the pieces' vertex integrals (one entry alone is
+        // up to 864 of them)
+        if constexpr (METAL) {
+            for (int q = 0; q < sNcut; q++) {
+                const int item = sQueue[kWPairs * kWFreqs - 1 - q];
+                const int pi = (item >> 2) & (kWPairs - 1), f = fc + (item >> 2) / kWPairs;
+                const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
+                const bool conj_pair = dl == 0.0 && om.x == 0.0;
+                __syncthreads();
+                if (tid < 24) {
+                    double e4[4], b4[4], a4[4];
+                    bool all_in = true, none_b = true, none_a = true;
+                    int iv = 0, n = 0;
+                    Piece pc[kMaxPieces];
+#pragma unroll
+                    for (int v = 0; v < 4; v++) {
+                        const int sl = c_tetra.slot[tid][v];
+                        e4[v] = sE[sl][pi];
+                        b4[v] = sB[sl][pi];
+                        a4[v] = sA[sl][pi];
+                        if (sl == kTet.self) iv = v;
+                        all_in = all_in && b4[v] < ef && a4[v] > ef;
+                        none_b = none_b && !(b4[v] < ef);
+                        none_a = none_a && !(a4[v] > ef);
+                    }
+                    if (all_in) {
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            pc[0].e[v] = e4[v];
+                            pc[0].lam[v] = v == iv ? 1.0 : 0.0;
+                        }
+                        n = 1;
+                    } else if (!none_b && !none_a) {
+                        clipped_pieces(e4, b4, a4, ef, iv, pc, n);
+                    }
+                    // place of this tetrahedron's pieces: the counts before it
+                    int at = n;
+#pragma unroll
+                    for (int d = 1; d < 32; d <<= 1) {
+                        const int o = __shfl_up(at, d);
+                        if (tid >= d) at += o;
+                    }
+                    if (tid == 23) sNpc = at;
+                    at -= n;
+                    for (int i = 0; i < n; i++) sPc[at + i] = pc[i];
+                }
+                __syncthreads();
+                const int units = 4 * sNpc;
+                double2 x = make_double2(0.0, 0.0);
+                for (int zi = 0; zi < 2; zi++) {
+                    if (!(item >> zi & 1)) continue;
+                    const double2 zz = zi ? make_double2(-om.x, -om.y + dl) : make_double2(om.x, om.y + dl);
+                    for (int u = tid; u < units; u += kWThreads) {
+                        const Piece &pc = sPc[u >> 2];
+                        const double lam = pc.lam[u & 3];
+                        if (lam == 0.0) continue;
+                        double xs[5];
+                        double2 ls[5];
+#pragma unroll
+                        for (int v = 0; v < 4; v++) {
+                            xs[v] = pc.e[v];
+                            ls[v] = clog_d(make_double2(zz.x - xs[v], zz.y));
+                        }
+                        xs[4] = pc.e[u & 3];
+                        ls[4] = (u & 3) == 0 ? ls[0] : (u & 3) == 1 ? ls[1] : (u & 3) == 2 ? ls[2] : ls[3];
+                        sort5(xs, ls);
+                        const double2 d = dd4_sorted(zz, xs, ls);
+                        x.x += lam * d.x;
+                        x.y += lam * d.y;
+                    }
+                }
+#pragma unroll
+                for (int o = 1; o < 64; o <<= 1) {
+                    x.x += __shfl_xor(x.x, o);
+                    x.y += __shfl_xor(x.y, o);
+                }
+                if ((tid & 63) == 0) sSum[tid >> 6] = x;
+                __syncthreads();
+                if (tid == 0) {
+                    x = cadd(cadd(sSum[0], sSum[1]), cadd(sSum[2], sSum[3]));
+                    if (conj_pair) x = make_double2(2.0 * x.x, 0.0);
+                    double2 *o = w + (long)f * npair + p0 + pi;
+                    *o = cadd(*o, cscale(x, sFac[pi] * (1.0 / 6.0)));
+                }
+            }
+        }
+        __syncthreads();
+    }
+}
+
+// X at the mesh point (RP_W_SAMPLING), one thread per (pair, frequency).
+__global__ void __launch_bounds__(256)
+k_weights_sampling(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T,
+                   int o0, int nO, int e0, int nE, int k0, long npair, int nfreq, const double2 *freq, double delta,
+                   double2 *w)
+{
+    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= npair * nfreq) return;
     const int f = (int)(t / npair);
     const long p = t - (long)f * npair;
@@ -406,87 +796,9 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
     const double ha = 1.0 / kHartreeEv;
     const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
     const double dl = delta * ha;
-    const double2 z = make_double2(om.x, om.y + dl);
-    const double2 zp = make_double2(-om.x, -om.y + dl);
     const int kq = (mesh_wrap(n1 + q1, K1) * K2 + mesh_wrap(n2 + q2, K2)) * K3 + mesh_wrap(n3 + q3, K3);
-    double2 x;
-    if (mode == RP_W_SAMPLING) {
-        const double e = (E[(long)kq * nband + a] - E[(long)k * nband + b]) * ha;
-        x = cadd(crecip(make_double2(z.x - e, z.y)), crecip(make_double2(zp.x - e, zp.y)));
-    } else {
-#pragma unroll
-        for (int j = 0; j < 15; j++) {
-            const int code = kTet.nbr[j];
-            const int m1 = n1 + code / 9 - 1, m2 = n2 + (code / 3) % 3 - 1, m3 = n3 + code % 3 - 1;
-            const int kv = (mesh_wrap(m1, K1) * K2 + mesh_wrap(m2, K2)) * K3 + mesh_wrap(m3, K3);
-            const int kvq = (mesh_wrap(m1 + q1, K1) * K2 + mesh_wrap(m2 + q2, K2)) * K3 + mesh_wrap(m3 + q3, K3);
-            const double eb = E[(long)kv * nband + b] * ha, ea = E[(long)kvq * nband + a] * ha;
-            eR[j] = (E[(long)kvq * nband + a] - E[(long)kv * nband + b]) * ha;
-            if constexpr (METAL) {
-                sB[j][tid] = eb;
-                sA[j][tid] = ea;
-            }
-        }
-        // on the imaginary axis without broadening z' = z*, and since the
-        // corner energies are real I_v(z*) = conj(I_v(z)): x = 2 Re sum I_v(z)/6
-        const bool conj_pair = dl == 0.0 && om.x == 0.0;
-        x = make_double2(0.0, 0.0);
-        for (int zi = 0; zi < (conj_pair ? 1 : 2); zi++) {
-            const double2 zz = zi ? zp : z;
-#pragma unroll
-            for (int j = 0; j < 15; j++) sL[j][tid] = clog_d(make_double2(zz.x - eR[j], zz.y));
-            for (int tt = 0; tt < 24; tt++) {
-                if constexpr (METAL) {
-                    double e4[4], b4[4], a4[4];
-                    bool all_in = true, none_b = true, none_a = true;
-                    int iv = 0;
-#pragma unroll
-                    for (int v = 0; v < 4; v++) {
-                        const int sl = c_tetra.slot[tt][v];
-                        e4[v] = eR[sl];
-                        b4[v] = sB[sl][tid];
-                        a4[v] = sA[sl][tid];
-                        if (sl == kTet.self) iv = v;
-                        all_in = all_in && b4[v] < ef && a4[v] > ef;
-                        none_b = none_b && !(b4[v] < ef);
-                        none_a = none_a && !(a4[v] > ef);
-                    }
-                    if (none_b || none_a) continue;
-                    if (!all_in) {
-                        x = cadd(x, clipped_vertex_integral(zz, e4, b4, a4, ef, iv));
-                        continue;
-                    }
-                }
-                double xs[5];
-                double2 ls[5];
-#pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const int sl = c_tetra.slot[tt][v];
-                    xs[v] = eR[sl];
-                    ls[v] = sL[sl][tid];
-                }
-                xs[4] = eR[kTet.self];
-                ls[4] = sL[kTet.self][tid];
-                // sorting network on five keys, carrying the logarithms
-#define RP_CSWAP(i, j)                                                                             \
-    {                                                                                              \
-        const bool sw_ = xs[j] < xs[i];                                                            \
-        const double xi_ = xs[i], xj_ = xs[j];                                                     \
-        const double2 li_ = ls[i], lj_ = ls[j];                                                    \
-        xs[i] = sw_ ? xj_ : xi_;                                                                   \
-        xs[j] = sw_ ? xi_ : xj_;                                                                   \
-        ls[i] = sw_ ? lj_ : li_;                                                                   \
-        ls[j] = sw_ ? li_ : lj_;                                                                   \
-    }
-                RP_CSWAP(0, 1) RP_CSWAP(3, 4) RP_CSWAP(2, 4) RP_CSWAP(2, 3) RP_CSWAP(0, 3)
-                RP_CSWAP(0, 2) RP_CSWAP(1, 4) RP_CSWAP(1, 3) RP_CSWAP(1, 2)
-#undef RP_CSWAP
-                x = cadd(x, dd4_sorted(zz, xs, ls));
-            }
-        }
-        if (conj_pair) x = make_double2(2.0 * x.x, 0.0);
-        x = cscale(x, 1.0 / 6.0);
-    }
+    const double e = (E[(long)kq * nband + a] - E[(long)k * nband + b]) * ha;
+    const double2 x = cadd(crecip(make_double2(om.x - e, om.y + dl)), crecip(make_double2(-om.x - e, -om.y + dl)));
     double fac = 2.0 / (double)(K1 * K2 * K3);
     if (T) fac *= 1.0 - T[(long)kq * nband + a] * T[(long)k * nband + b];
     w[t] = cscale(x, fac);
@@ -625,15 +937,26 @@ void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nban
     const long npair = (long)(k1 - k0) * (e1 - e0) * (o1 - o0);
     const long tot = npair * nfreq;
     if (tot == 0) return;
-    const dim3 grid((unsigned)((tot + kWThreads - 1) / kWThreads));
-    if (mode == RP_W_TETRA_METAL)
-        hipLaunchKernelGGL(k_weights<true>, grid, dim3(kWThreads), 0, s, kmesh[0], kmesh[1], kmesh[2], iq[0], iq[1],
-                           iq[2], nband, E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, freq_eV, delta_eV,
-                           (int)RP_W_TETRA, ef_eV / kHartreeEv, w);
-    else
-        hipLaunchKernelGGL(k_weights<false>, grid, dim3(kWThreads), 0, s, kmesh[0], kmesh[1], kmesh[2], iq[0], iq[1],
-                           iq[2], nband, E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, freq_eV, delta_eV,
-                           mode, 0.0, w);
+    if (mode == RP_W_SAMPLING) {
+        hipLaunchKernelGGL(k_weights_sampling, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, kmesh[0], kmesh[1],
+                           kmesh[2], iq[0], iq[1], iq[2], nband, E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq,
+                           freq_eV, delta_eV, w);
+        return;
+    }
+    // frequencies per workgroup: all of them where the pairs alone give two
+    // workgroups per CU (each forms its pairs' moments once), else fewer, down
+    // to two: the integrals of the near frequencies are the longest part
+    const long blocks = (npair + kWPairs - 1) / kWPairs;
+    const int want = (int)std::min<long>((nfreq + kWMinFreqs - 1) / kWMinFreqs, std::max<long>(1, 512 / blocks));
+    const int fper = (nfreq + want - 1) / want;
+    const dim3 grid((unsigned)blocks, (unsigned)((nfreq + fper - 1) / fper));
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(kWThreads), 0, s, kmesh[0], kmesh[1], kmesh[2], iq[0], iq[1], iq[2], nband,
+                           E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, fper, freq_eV, delta_eV,
+                           ef_eV / kHartreeEv, w);
+    };
+    if (mode == RP_W_TETRA_METAL) go(k_weights<true>);
+    else go(k_weights<false>);
 }
 
 void launch_fermi_plasma(hipStream_t s, const int kmesh[3], int nband, const double *E_eV, const double *T, int b0,
