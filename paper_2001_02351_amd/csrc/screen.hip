@@ -71,111 +71,252 @@ __global__ void k_eps(int nfreq, int ng, const double *vs, const double2 *chi, d
 typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int kGjNb = 64;            // panel width
-constexpr int kGjPivotThreads = 1024;
-constexpr int kGjElimRows = 16;      // rows per elimination workgroup (4 per thread)
 
-// (|v|, row) of the larger pivot candidate; ties go to the lower row
-__device__ __forceinline__ void pivot_max(double &m, int &r, double om, int orow)
+// The panel being worked on sits in a buffer of its own, column by column:
+// pb [f][64][ng] (column c0 + j, row i at j ng + i).  Its steps go down columns,
+// and in the row-major matrix each element of a column is a line (and, for
+// N = 1500, a page) of its own.
+
+// Panel [0, nb) of the matrices into pb; one workgroup per 64 rows.
+__global__ void __launch_bounds__(256)
+k_gj_first(int ng, int nb, const double2 *a, double2 *pb)
 {
-    if (om > m || (om == m && orow < r)) { m = om; r = orow; }
+    __shared__ double2 t[16][64 + 1];
+    const int f = blockIdx.y, tid = threadIdx.x, r0 = blockIdx.x * 64;
+    const double2 *A = a + (long)f * ng * ng;
+    double2 *B = pb + (long)f * kGjNb * ng;
+    for (int k0 = 0; k0 < nb; k0 += 16) {
+        for (int e = tid; e < 64 * 16; e += 256) {
+            const int r = e >> 4, k = e & 15;
+            if (r0 + r < ng && k0 + k < nb) t[k][r] = A[(long)(r0 + r) * ng + k0 + k];
+        }
+        __syncthreads();
+        for (int e = tid; e < 64 * 16; e += 256) {
+            const int k = e >> 6, r = e & 63;
+            if (r0 + r < ng && k0 + k < nb) B[(long)(k0 + k) * ng + r0 + r] = t[k][r];
+        }
+        __syncthreads();
+    }
 }
 
-// Step c of panel [c0, c0 + nb), first half, one block per matrix: pivot
-// search over rows >= c of column c, swap of the full rows r and c, and the
-// scaled pivot row's panel entries into prow[f][0 .. nb) (1/a_cc in column
-// c itself).
-__global__ void __launch_bounds__(kGjPivotThreads)
-k_gj_pivot(int ng, int c0, int nb, int c, double2 *a, double2 *prow, int *piv, int *flag)
+// Columns [cs, cs + wc) of panel [c0, c0 + nb), wc <= W: the pivoted steps, one
+// workgroup per matrix with the N x wc block in registers (thread t holds rows
+// t + NT q, q < R).  Then the steps' row swaps on the panel's other columns,
+// whose pivot rows go to rkp [f][W][64] for the update of those columns
+// (k_gj_inner).
+//
+// What bounds it is the chain of N steps on one CU per matrix, each a search
+// over a column, a workgroup barrier and one row update: about 2 us a step for
+// N = 1500, against 16 us for a search launch and an elimination launch over
+// the whole panel per step.  More columns per call mean fewer calls (each also
+// reads and writes its columns and updates the panel's others, about 15 us
+// together), as many as the registers hold: see launch_invert.  Inversions:
+// 20 x 1500: 38.2 -> 20.9 ms, 4 x 6000: 258 -> 206 ms, 16 x 300: 3.2 -> 1.1 ms,
+// 10 x 89: 0.92 -> 0.35 ms (eps and W included).
+//
+// The pivot is the row of largest |re| + |im| (within a factor sqrt 2 of the
+// largest modulus): that number with its last 13 bits replaced by 8191 - row is
+// a key whose maximum is the pivot, the lower row on a tie (a non-finite entry
+// counts as the largest double and is reported when it is used).
+template <int CTRL, int ROWS> __device__ __forceinline__ double dpp_max(double v)
 {
-    constexpr int NWV = kGjPivotThreads / 64;
-    __shared__ double bv[NWV];
-    __shared__ int bi[NWV];
-    const int f = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    double2 *A = a + (long)f * ng * ng;
-    double best = -1.0;
-    int bidx = c;
-    for (int i = c + tid; i < ng; i += kGjPivotThreads) {
-        const double2 v = A[(long)i * ng + c];
-        const double m = isfinite(v.x) && isfinite(v.y) ? hypot(v.x, v.y) : INFINITY;
-        pivot_max(best, bidx, m, i);
-    }
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, true);
+    return fmax(v, __longlong_as_double((long long)hi << 32 | (unsigned)lo));
+}
+
+// largest of a row of 16 lanes' non-negative keys, in its last lane
+__device__ __forceinline__ double row_max(double v)
+{
+    v = dpp_max<0x111, 0xf>(v);   // row_shr 1, 2, 4, 8
+    v = dpp_max<0x112, 0xf>(v);
+    v = dpp_max<0x114, 0xf>(v);
+    return dpp_max<0x118, 0xf>(v);
+}
+
+template <int LANE> __device__ __forceinline__ double read_lane(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)b, LANE), hi = __builtin_amdgcn_readlane((int)(b >> 32), LANE);
+    return __longlong_as_double((long long)hi << 32 | (unsigned)lo);
+}
+
+__device__ __forceinline__ int key_row(double key) { return 8191 - (int)(__double_as_longlong(key) & 8191); }
+
+template <int R, int W, int NT>
+__global__ void __launch_bounds__(NT)
+k_gj_panel(int ng, int c0, int nb, int cs, int wc, double2 *pb, double2 *rkp, int *piv, int *flag)
+{
+    constexpr int NW = NT / 64;
+    // two sets, used in turn: a step needs one barrier
+    __shared__ double sKey[2][NW];
+    __shared__ double2 sCand[2][NW][W], sC[2][W];   // each wave's candidate row, and row c
+    __shared__ int sPiv[W];
+    const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    double2 *B = pb + (long)f * kGjNb * ng;
+    double2 v[R][W];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) pivot_max(best, bidx, __shfl_xor(best, o), __shfl_xor(bidx, o));
-    if (lane == 0) {
-        bv[wave] = best;
-        bi[wave] = bidx;
-    }
-    __syncthreads();
-    best = bv[0];
-    bidx = bi[0];
+    for (int j = 0; j < W; j++)
 #pragma unroll
-    for (int w = 1; w < NWV; w++) pivot_max(best, bidx, bv[w], bi[w]);
-    const int r = bidx;
-    if (tid == 0) {
-        piv[(long)f * ng + c] = r;
-        if (!isfinite(best)) atomicOr(flag, kFlagNonFinite);
-        else if (!(best > kPivotFloor)) atomicOr(flag, kFlagZeroPivot);
-    }
-    if (r != c) {
-        for (int j = tid; j < ng; j += kGjPivotThreads) {
-            const double2 t = A[(long)c * ng + j];
-            A[(long)c * ng + j] = A[(long)r * ng + j];
-            A[(long)r * ng + j] = t;
+        for (int q = 0; q < R; q++) {
+            const int i = tid + q * NT;
+            v[q][j] = i < ng && j < wc ? B[(long)(cs - c0 + j) * ng + i] : make_double2(0.0, 0.0);
+        }
+    // One loop body for every step (unrolled, the code is fetched as slowly as
+    // the steps run): the step's column is always v[.][0], and the columns move
+    // down by one with each step, so that W of them leave every one in place.
+#pragma unroll 1
+    for (int s = 0; s < W; s++) {
+        if (s >= wc) {
+#pragma unroll
+            for (int q = 0; q < R; q++) {
+                const double2 first = v[q][0];
+#pragma unroll
+                for (int j = 0; j + 1 < W; j++) v[q][j] = v[q][j + 1];
+                v[q][W - 1] = first;
+            }
+            continue;
+        }
+        const int c = cs + s, set = s & 1;
+        double key = 0.0;
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const int i = tid + q * NT;
+            const double m = fmin(fabs(v[q][0].x) + fabs(v[q][0].y), 1.79e308);   // NaN and infinity: 1.79e308
+            const double k = __longlong_as_double((__double_as_longlong(m) & ~8191ll) | (8191 - i));
+            key = fmax(key, i >= c && i < ng ? k : 0.0);
+        }
+        key = dpp_max<0x142, 0xa>(row_max(key));   // row_bcast 15 and 31: across the rows
+        key = read_lane<63>(dpp_max<0x143, 0xc>(key));
+        const int mine = key_row(key);
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            if (tid + q * NT == mine)
+#pragma unroll
+                for (int j = 0; j < W; j++) sCand[set][wave][j] = v[q][j];
+            if (tid + q * NT == c)
+#pragma unroll
+                for (int j = 0; j < W; j++) sC[set][j] = v[q][j];
+        }
+        if (lane == 0) sKey[set][wave] = key;
+        __syncthreads();
+        const int r = key_row(read_lane<15>(row_max(sKey[set][lane % NW])));
+        const double2 *sP = sCand[set][(r % NT) >> 6];
+        const double2 p = sP[0];
+        const double den = p.x * p.x + p.y * p.y, rd = 1.0 / den;
+        const double2 ip = make_double2(p.x * rd, -p.y * rd);
+        if (tid == 0) {
+            sPiv[s] = r;
+            piv[(long)f * ng + c] = r;
+            if (!(den > 4.0 * kPivotFloor * kPivotFloor) || !isfinite(den)) {
+                const double m = hypot(p.x, p.y);
+                if (!isfinite(m)) atomicOr(flag, kFlagNonFinite);
+                else if (!(m > kPivotFloor)) atomicOr(flag, kFlagZeroPivot);
+            }
+        }
+        // row c takes the pivot row times 1/p (1/p itself in column c); the
+        // others, row r now holding the former row c, lose their multiple of it
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const int i = tid + q * NT;
+            if (i == r && r != c)
+#pragma unroll
+                for (int j = 0; j < W; j++) v[q][j] = sC[set][j];
+            if (i == c) {
+#pragma unroll
+                for (int j = 1; j < W; j++) v[q][j - 1] = cmul(sP[j], ip);
+                v[q][W - 1] = ip;
+            } else {
+                const double2 m = cmul(v[q][0], ip);
+#pragma unroll
+                for (int j = 1; j < W; j++) v[q][j - 1] = csub(v[q][j], cmul(m, sP[j]));
+                v[q][W - 1] = make_double2(-m.x, -m.y);
+            }
         }
     }
+#pragma unroll
+    for (int j = 0; j < W; j++)
+#pragma unroll
+        for (int q = 0; q < R; q++) {
+            const int i = tid + q * NT;
+            if (i < ng && j < wc) B[(long)(cs - c0 + j) * ng + i] = v[q][j];
+        }
     __syncthreads();
-    const double2 p = A[(long)c * ng + c];
-    const double den = p.x * p.x + p.y * p.y;
-    const double2 ip = make_double2(p.x / den, -p.y / den);
-    if (tid < nb) {
-        const int j = c0 + tid;
-        prow[(long)f * kGjNb + tid] = (j == c) ? ip : cmul(A[(long)c * ng + j], ip);
+    // the swaps on the panel's other columns: rows cs + s and sPiv[s] (some
+    // twice, with the same values), each read where the swaps took it from
+    constexpr int PER = (2 * W * kGjNb + NT - 1) / NT;
+    double2 x[PER];
+    int dst[PER];
+    const int slot = tid % (2 * W);
+    int row = slot < W ? cs + slot : cs;
+    if (slot >= W && slot - W < wc) row = sPiv[slot - W];
+    // past the last step, or a pivot from the block's own rows
+    const bool moves = slot < W ? slot < wc : row >= cs + wc;
+    int src = row;
+    for (int s = wc - 1; s >= 0; s--) {
+        const int r = sPiv[s];
+        src = src == cs + s ? r : src == r ? cs + s : src;
+    }
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        const int j = (tid + e * NT) / (2 * W), col = c0 + j;
+        dst[e] = -1;
+        if (!moves || j >= nb || (col >= cs && col < cs + wc)) continue;
+        dst[e] = row;
+        x[e] = B[(long)j * ng + src];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        const int j = (tid + e * NT) / (2 * W);
+        if (dst[e] < 0) continue;
+        if (dst[e] < cs + wc) rkp[((long)f * W + dst[e] - cs) * kGjNb + j] = x[e];
+        else B[(long)j * ng + dst[e]] = x[e];
     }
 }
 
-// Step c, second half: the panel columns of every row, grid (row blocks of
-// kGjElimRows, matrices).  Row c takes the scaled pivot row; column c of the
-// other rows takes -a_ic/a_cc; the other entries a_ij - a_ic prow_j.  Each
-// thread reads the a_ic of its rows before any thread of the block (which
-// owns those rows whole) writes column c.
+// After panel [c0, c0 + nb): its row swaps on the columns outside it, 32
+// columns per workgroup (all their rows are read before any is written).  The
+// pivot rows go to rk [f][64][ng] for the update of those columns.
 __global__ void __launch_bounds__(256)
-k_gj_elim(int ng, int c0, int nb, int c, double2 *a, const double2 *prow)
+k_gj_rows(int ng, int c0, int nb, double2 *a, const int *piv, double2 *rk)
 {
-    const int f = blockIdx.y, tid = threadIdx.x, jj = tid & 63, rr = tid >> 6;
+    constexpr int COLS = 32, PER = 2 * kGjNb * COLS / 256;
+    __shared__ int sPiv[kGjNb], sDst[2 * kGjNb], sSrc[2 * kGjNb];
+    const int f = blockIdx.y, tid = threadIdx.x;
     double2 *A = a + (long)f * ng * ng;
-    const double2 *pr = prow + (long)f * kGjNb;
-    const int i0 = blockIdx.x * kGjElimRows + rr;
-    double2 fi[kGjElimRows / 4];
-#pragma unroll
-    for (int q = 0; q < kGjElimRows / 4; q++) {
-        const int i = i0 + 4 * q;
-        fi[q] = i < ng ? A[(long)i * ng + c] : make_double2(0.0, 0.0);
+    if (tid < nb) sPiv[tid] = piv[(long)f * ng + c0 + tid];
+    __syncthreads();
+    if (tid < 2 * kGjNb) {
+        const int s0 = tid % kGjNb;
+        int row = -1, src = -1;
+        if (s0 < nb) {
+            row = tid < kGjNb ? c0 + s0 : sPiv[s0];
+            if (tid >= kGjNb && row < c0 + nb) row = -1;
+            src = row;
+            for (int s = nb - 1; s >= 0; s--) src = src == c0 + s ? sPiv[s] : src == sPiv[s] ? c0 + s : src;
+        }
+        sDst[tid] = row;
+        sSrc[tid] = src;
     }
     __syncthreads();
-    if (jj >= nb) return;
-    const int j = c0 + jj;
-    const double2 pj = pr[jj], ip = pr[c - c0];
+    const int j = blockIdx.x * COLS + tid % COLS;
+    const bool on = j < ng && !(j >= c0 && j < c0 + nb);
+    double2 x[PER];
 #pragma unroll
-    for (int q = 0; q < kGjElimRows / 4; q++) {
-        const int i = i0 + 4 * q;
-        if (i >= ng) continue;
-        double2 *x = A + (long)i * ng + j;
-        double2 v;
-        if (i == c) v = pj;
-        else v = (j == c) ? cmul(make_double2(-fi[q].x, -fi[q].y), ip) : csub(*x, cmul(fi[q], pj));
-        *x = v;
+    for (int e = 0; e < PER; e++) {
+        const int slot = tid / COLS + e * (256 / COLS);
+        if (on && sDst[slot] >= 0) x[e] = A[(long)sSrc[slot] * ng + j];
     }
-}
-
-// After the panel: its pivot rows (all columns) into rk [f][nb][ng] for the
-// update of the other columns.
-__global__ void k_gj_saverows(int ng, int c0, int nb, const double2 *a, double2 *rk)
-{
-    const int f = blockIdx.y;
-    const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (long)nb * ng) return;
-    const int kk = (int)(t / ng), j = (int)(t - (long)kk * ng);
-    rk[((long)f * kGjNb + kk) * ng + j] = a[(long)f * ng * ng + (long)(c0 + kk) * ng + j];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+        const int slot = tid / COLS + e * (256 / COLS);
+        if (!on || sDst[slot] < 0) continue;
+        if (slot < kGjNb) rk[((long)f * kGjNb + slot) * ng + j] = x[e];
+        else A[(long)sDst[slot] * ng + j] = x[e];
+    }
 }
 
 __device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
@@ -183,27 +324,114 @@ __device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
 }
 
-// Update of the columns outside panel [c0, c0 + nb) (see the header):
-//   A[i][j] = sum_k A[i][c0 + k] rk[k][j] + (i outside the panel rows ? A[i][j] : 0)
+// After the steps of columns [cs, cs + wc) of panel [c0, c0 + nb): the panel's
+// other columns,
+//   x_ij = sum_k x_i,cs+k rkp[k][j] + (i outside rows [cs, cs + wc) ? x_ij : 0).
+// One workgroup per 64 rows; the product runs transposed (matrix rows: columns
+// j of the panel, matrix columns: rows i), so that the results of 16 lanes are
+// 16 neighbours of a column.  wc <= KC: one chunk, bound by the loads' latency.
+template <int W, int KC>
+__global__ void __launch_bounds__(256)
+k_gj_inner(int ng, int c0, int nb, int cs, int wc, double2 *pb, const double2 *rkp)
+{
+    __shared__ double2 sR[KC][64];
+    __shared__ double2 sP[KC][64];
+    const int f = blockIdx.y, tid = threadIdx.x, rt0 = blockIdx.x * 64;
+    double2 *B = pb + (long)f * kGjNb * ng;
+    const double2 *R = rkp + (long)f * W * kGjNb;
+    const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int wr = (wave >> 1) * 32, wc0 = (wave & 1) * 32;
+    double2 x0[2][2][4];
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+        for (int bc = 0; bc < 2; bc++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int j = wr + rb * 16 + lk + 4 * r, i = rt0 + wc0 + bc * 16 + li;
+                x0[rb][bc][r] = make_double2(0.0, 0.0);
+                if (j < nb && i < ng && (i < cs || i >= cs + wc)) x0[rb][bc][r] = B[(long)j * ng + i];
+            }
+#pragma unroll
+    for (int e = tid; e < KC * 64; e += 256) {
+        const int k = e >> 6, x = e & 63;
+        sR[k][x] = k < wc && x < nb ? R[k * kGjNb + x] : make_double2(0.0, 0.0);
+        sP[k][x] = k < wc && rt0 + x < ng ? B[(long)(cs - c0 + k) * ng + rt0 + x] : make_double2(0.0, 0.0);
+    }
+    __syncthreads();
+    d4 accR[2][2], accI[2][2];
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+        for (int bc = 0; bc < 2; bc++) {
+            accR[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
+            accI[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+#pragma unroll
+    for (int k0 = 0; k0 < KC; k0 += 4) {
+        double2 x[2], y[2];
+#pragma unroll
+        for (int rb = 0; rb < 2; rb++) x[rb] = sR[k0 + lk][wr + rb * 16 + li];
+#pragma unroll
+        for (int bc = 0; bc < 2; bc++) y[bc] = sP[k0 + lk][wc0 + bc * 16 + li];
+#pragma unroll
+        for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+            for (int bc = 0; bc < 2; bc++) {
+                accR[rb][bc] = mfma64(x[rb].x, y[bc].x, accR[rb][bc]);
+                accR[rb][bc] = mfma64(-x[rb].y, y[bc].y, accR[rb][bc]);
+                accI[rb][bc] = mfma64(x[rb].x, y[bc].y, accI[rb][bc]);
+                accI[rb][bc] = mfma64(x[rb].y, y[bc].x, accI[rb][bc]);
+            }
+    }
+#pragma unroll
+    for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+        for (int bc = 0; bc < 2; bc++)
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                const int j = wr + rb * 16 + lk + 4 * r, i = rt0 + wc0 + bc * 16 + li;
+                if (j >= nb || i >= ng || (c0 + j >= cs && c0 + j < cs + wc)) continue;
+                B[(long)j * ng + i] = cadd(x0[rb][bc][r], make_double2(accR[rb][bc][r], accI[rb][bc][r]));
+            }
+}
+
+// Update of the columns outside panel [c0, c0 + nb) (see the header), P in pb:
+//   A[i][j] = sum_k pb[k][i] rk[k][j] + (i outside the panel rows ? A[i][j] : 0)
 // A 256-thread block owns a 64x64 tile of one matrix; each wave a 32x32
 // sub-tile (2x2 blocks of 16x16) on v_mfma_f64_16x16x4f64 (A operand lane
 // i + 16k, B operand lane j + 16k, result register r of lane l at row
-// l / 16 + 4 r, column l % 16).  The panel columns of the tile's rows and the
-// pivot rows of its columns are staged in LDS.
+// l / 16 + 4 r, column l % 16).  The tiles of the next panel's columns go to
+// its buffer pbn instead of A, those of this panel's columns copy it back.
 __global__ void __launch_bounds__(256, 3)
-k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *rk)
+k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *pb, double2 *pbn, const double2 *rk)
 {
     // the panel's 64 columns pass through LDS in chunks of 16, so that a CU
     // holds several workgroups and one's loads overlap another's matrix work;
     // the registers are held to three waves per SIMD (three workgroups per
     // CU; four would spill)
     constexpr int KC = 16;
-    __shared__ double2 sP[64][KC + 1];
+    __shared__ double2 sP[KC][64 + 1];
     __shared__ double2 sR[KC][64];
     const int f = blockIdx.z, tid = threadIdx.x;
     const int rt0 = blockIdx.y * 64, ct0 = blockIdx.x * 64;
-    if (ct0 >= c0 && ct0 + 64 <= c0 + nb) return;   // tile inside the panel columns
     double2 *A = a + (long)f * ng * ng;
+    const double2 *B = pb + (long)f * kGjNb * ng;
+    if (ct0 == c0) {
+        for (int k0 = 0; k0 < nb; k0 += KC) {
+            for (int e = tid; e < KC * 64; e += 256) {
+                const int k = e >> 6, r = e & 63;
+                if (rt0 + r < ng && k0 + k < nb) sP[k][r] = B[(long)(k0 + k) * ng + rt0 + r];
+            }
+            __syncthreads();
+            for (int e = tid; e < KC * 64; e += 256) {
+                const int r = e / KC, k = e % KC;
+                if (rt0 + r < ng && k0 + k < nb) A[(long)(rt0 + r) * ng + c0 + k0 + k] = sP[k][r];
+            }
+            __syncthreads();
+        }
+        return;
+    }
     const double2 *R = rk + (long)f * kGjNb * ng;
     const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
@@ -211,9 +439,9 @@ k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *rk)
 #pragma unroll
     for (int rb = 0; rb < 2; rb++)
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++) {
-            accR[rb][cb] = d4{0.0, 0.0, 0.0, 0.0};
-            accI[rb][cb] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int bc = 0; bc < 2; bc++) {
+            accR[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
+            accI[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
         }
     // each thread moves 4 panel and 4 pivot-row elements of a chunk; the next
     // chunk's are loaded into registers before the current chunk's matrix
@@ -223,11 +451,9 @@ k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *rk)
     auto fetch = [&](int kc) {
 #pragma unroll
         for (int q = 0; q < PER; q++) {
-            const int e = tid + q * 256;
-            const int rr = e / KC, k = e - rr * KC, i = rt0 + rr;
-            pp[q] = (i < ng && kc + k < nb) ? A[(long)i * ng + c0 + kc + k] : make_double2(0.0, 0.0);
-            const int k2 = e >> 6, cc = e & 63, j = ct0 + cc;
-            pr[q] = (kc + k2 < nb && j < ng) ? R[(long)(kc + k2) * ng + j] : make_double2(0.0, 0.0);
+            const int e = tid + q * 256, k = e >> 6, x = e & 63;
+            pp[q] = kc + k < nb && rt0 + x < ng ? B[(long)(kc + k) * ng + rt0 + x] : make_double2(0.0, 0.0);
+            pr[q] = kc + k < nb && ct0 + x < ng ? R[(long)(kc + k) * ng + ct0 + x] : make_double2(0.0, 0.0);
         }
     };
     fetch(0);
@@ -235,7 +461,7 @@ k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *rk)
 #pragma unroll
         for (int q = 0; q < PER; q++) {
             const int e = tid + q * 256;
-            sP[e / KC][e % KC] = pp[q];
+            sP[e >> 6][e & 63] = pp[q];
             sR[e >> 6][e & 63] = pr[q];
         }
         __syncthreads();
@@ -244,32 +470,40 @@ k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *rk)
         for (int k0 = 0; k0 < KC; k0 += 4) {
             double2 x[2], y[2];
 #pragma unroll
-            for (int rb = 0; rb < 2; rb++) x[rb] = sP[wr + rb * 16 + li][k0 + lk];
+            for (int rb = 0; rb < 2; rb++) x[rb] = sP[k0 + lk][wr + rb * 16 + li];
 #pragma unroll
-            for (int cb = 0; cb < 2; cb++) y[cb] = sR[k0 + lk][wc + cb * 16 + li];
+            for (int bc = 0; bc < 2; bc++) y[bc] = sR[k0 + lk][wc + bc * 16 + li];
 #pragma unroll
             for (int rb = 0; rb < 2; rb++)
 #pragma unroll
-                for (int cb = 0; cb < 2; cb++) {
-                    accR[rb][cb] = mfma64(x[rb].x, y[cb].x, accR[rb][cb]);
-                    accR[rb][cb] = mfma64(-x[rb].y, y[cb].y, accR[rb][cb]);
-                    accI[rb][cb] = mfma64(x[rb].x, y[cb].y, accI[rb][cb]);
-                    accI[rb][cb] = mfma64(x[rb].y, y[cb].x, accI[rb][cb]);
+                for (int bc = 0; bc < 2; bc++) {
+                    accR[rb][bc] = mfma64(x[rb].x, y[bc].x, accR[rb][bc]);
+                    accI[rb][bc] = mfma64(x[rb].x, y[bc].y, accI[rb][bc]);
+                }
+#pragma unroll
+            for (int rb = 0; rb < 2; rb++)
+#pragma unroll
+                for (int bc = 0; bc < 2; bc++) {
+                    accR[rb][bc] = mfma64(-x[rb].y, y[bc].y, accR[rb][bc]);
+                    accI[rb][bc] = mfma64(x[rb].y, y[bc].x, accI[rb][bc]);
                 }
         }
         __syncthreads();
     }
+    const bool next = ct0 == c0 + kGjNb;
+    double2 *N = pbn + (long)f * kGjNb * ng;
 #pragma unroll
     for (int rb = 0; rb < 2; rb++)
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++)
+        for (int bc = 0; bc < 2; bc++)
 #pragma unroll
             for (int r = 0; r < 4; r++) {
-                const int i = rt0 + wr + rb * 16 + lk + 4 * r, j = ct0 + wc + cb * 16 + li;
-                if (i >= ng || j >= ng || (j >= c0 && j < c0 + nb)) continue;
-                double2 v = make_double2(accR[rb][cb][r], accI[rb][cb][r]);
+                const int i = rt0 + wr + rb * 16 + lk + 4 * r, j = ct0 + wc + bc * 16 + li;
+                if (i >= ng || j >= ng) continue;
+                double2 v = make_double2(accR[rb][bc][r], accI[rb][bc][r]);
                 if (i < c0 || i >= c0 + nb) v = cadd(v, A[(long)i * ng + j]);
-                A[(long)i * ng + j] = v;
+                if (next) N[(long)(j - ct0) * ng + i] = v;
+                else A[(long)i * ng + j] = v;
             }
 }
 
@@ -320,25 +554,51 @@ void launch_eps(hipStream_t s, int nfreq, int ng, const double *vs, const double
                        eps, flag);
 }
 
-// the pivot rows of a panel [nfreq][kGjNb][ng], then the scaled pivot rows [nfreq][kGjNb]
-size_t invert_scratch_bytes(int ng, int nfreq) { return sizeof(double2) * (size_t)kGjNb * (ng + 1) * nfreq; }
+// two panels and the pivot rows of one, [nfreq][64][ng] each, then the pivot
+// rows of a few columns [nfreq][<= 16][64]
+size_t invert_scratch_bytes(int ng, int nfreq)
+{
+    return sizeof(double2) * (size_t)kGjNb * (3 * ng + 16) * nfreq;
+}
+
+template <int R, int W, int NT>
+static void panel_steps(hipStream_t s, int nfreq, int ng, int c0, int nb, double2 *pb, double2 *rkp, int *piv,
+                        int *flag)
+{
+    for (int cs = c0; cs < c0 + nb; cs += W) {
+        const int wc = std::min(W, c0 + nb - cs);
+        hipLaunchKernelGGL((k_gj_panel<R, W, NT>), dim3(nfreq), dim3(NT), 0, s, ng, c0, nb, cs, wc, pb, rkp, piv, flag);
+        if (nb > wc)
+            hipLaunchKernelGGL((k_gj_inner<W, (W > 4 ? W : 4)>), dim3((unsigned)((ng + 63) / 64), nfreq), dim3(256), 0,
+                               s, ng, c0, nb, cs, wc, pb, rkp);
+    }
+}
 
 void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, int *piv, int *flag)
 {
     const unsigned t = (unsigned)((ng + 63) / 64);
-    double2 *prow = scratch + (size_t)kGjNb * ng * nfreq;
-    const dim3 eg((unsigned)((ng + kGjElimRows - 1) / kGjElimRows), (unsigned)nfreq);
+    const size_t panel = (size_t)kGjNb * ng * nfreq;
+    double2 *pb = scratch, *pbn = scratch + panel, *rk = scratch + 2 * panel, *rkp = scratch + 3 * panel;
+    hipLaunchKernelGGL(k_gj_first, dim3(t, nfreq), dim3(256), 0, s, ng, std::min(kGjNb, ng), a, pb);
     for (int c0 = 0; c0 < ng; c0 += kGjNb) {
         const int nb = std::min(kGjNb, ng - c0);
-        for (int c = c0; c < c0 + nb; c++) {
-            hipLaunchKernelGGL(k_gj_pivot, dim3(nfreq), dim3(kGjPivotThreads), 0, s, ng, c0, nb, c, a, prow, piv,
-                               flag);
-            hipLaunchKernelGGL(k_gj_elim, eg, dim3(256), 0, s, ng, c0, nb, c, a, prow);
-        }
-        const long nrow = (long)nb * ng;
-        hipLaunchKernelGGL(k_gj_saverows, dim3((unsigned)((nrow + 255) / 256), (unsigned)nfreq), dim3(256), 0, s,
-                           ng, c0, nb, a, scratch);
-        hipLaunchKernelGGL(k_gj_update, dim3(t, t, nfreq), dim3(256), 0, s, ng, c0, nb, a, scratch);
+        // rows per thread x columns x threads: R W double2 values in registers
+        // without spilling; measured against the neighbouring choices at 300,
+        // 777, 1500, 2048, 3000 and 6000 (e.g. 6000: <6, 3, 1024> 203 ms,
+        // <12, 3, 512> 204, <6, 2, 1024> 205; 1500: <3, 16, 512> 21.5 ms)
+        if (ng <= 256) panel_steps<1, 16, 256>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 512) panel_steps<1, 16, 512>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 1024) panel_steps<2, 8, 512>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 1536) panel_steps<3, 8, 512>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 2048) panel_steps<2, 8, 1024>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 3072) panel_steps<3, 4, 1024>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else if (ng <= 4096) panel_steps<4, 4, 1024>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        else panel_steps<6, 3, 1024>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
+        if (ng > nb)
+            hipLaunchKernelGGL(k_gj_rows, dim3((unsigned)((ng + 31) / 32), nfreq), dim3(256), 0, s, ng, c0, nb, a, piv,
+                               rk);
+        hipLaunchKernelGGL(k_gj_update, dim3(t, t, nfreq), dim3(256), 0, s, ng, c0, nb, a, pb, pbn, rk);
+        std::swap(pb, pbn);
     }
     const long rows = (long)nfreq * ng;
     hipLaunchKernelGGL(k_gj_unswap, dim3((unsigned)((rows + 127) / 128)), dim3(128), 0, s, nfreq, ng, a,
