@@ -100,19 +100,21 @@ __global__ void k_scatter(const int *miller, const double2 *coef, int npw, int b
     u[(long)band * N1 * N2 * N3 + ((long)m1 * N2 + m2) * N3 + m3] = mkc<C>((T)c.x, (T)c.y);
 }
 
-// Counting sort of the plane-wave lists of the two band sets by grid plane:
-// block `set` lists the g < npw of plane j1 = m1 mod N1 at perm[set][off[j1]
-// .. off[j1 + 1]) (the order within a plane is free: every g has its own
-// grid point).  N1 <= 256.
+// Counting sort of the plane-wave lists of each k-point's two band sets by
+// grid plane: block (set, k-point) lists the g < npw of plane j1 = m1 mod N1 at
+// perm[k-point][set][off[j1] .. off[j1 + 1]) (the order within a plane is
+// free: every g has its own grid point).  N1 <= 256.
 __global__ void __launch_bounds__(256)
-k_plane_sort(const int *millerA, int npwA, const int *millerB, int npwB, int N1, int npw_max, int *perm, int *off)
+k_plane_sort(BandSource src, KGroup grp, int N1, int *perm, int *off)
 {
     __shared__ int cnt[256];
     const int set = blockIdx.x, tid = threadIdx.x;
-    const int *mil = set ? millerB : millerA;
-    const int npw = set ? npwB : npwA;
-    int *pm = perm + (long)set * npw_max;
-    int *of = off + set * (N1 + 1);
+    const KItem &it = grp.it[blockIdx.y];
+    const int *mil = src.miller + (long)(set ? it.kp : it.k) * src.npw_max * 3;
+    const int npw = set ? it.npwB : it.npwA;
+    const long list = 2 * (long)blockIdx.y + set;
+    int *pm = perm + list * src.npw_max;
+    int *of = off + list * (N1 + 1);
     for (int j = tid; j < N1; j += 256) cnt[j] = 0;
     __syncthreads();
     for (int g = tid; g < npw; g += 256) atomicAdd(&cnt[pmod(mil[3 * g], N1)], 1);
@@ -131,7 +133,7 @@ k_plane_sort(const int *millerA, int npwA, const int *millerB, int npwB, int N1,
     for (int g = tid; g < npw; g += 256) pm[atomicAdd(&cnt[pmod(mil[3 * g], N1)], 1)] = g;
 }
 
-// Axes 3 and 2 of the u-grids plane by plane in LDS: block (j1, band)
+// Axes 3 and 2 of the u-grids plane by plane in LDS: block (j1, band, k-point)
 // scatters the band's coefficients of plane j1 (from k_plane_sort) into a
 // zeroed N2 x N3 plane, transforms the rows that can hold a non-zero
 // coefficient (|m2| <= mmax2, as the pruned pass along axis 3 does), then
@@ -140,9 +142,8 @@ k_plane_sort(const int *millerA, int npwA, const int *millerB, int npwB, int N1,
 // as the zero fill, scatter and first two passes of fft3d_passes.
 template <typename C>
 __global__ void __launch_bounds__(256)
-k_ugrid_planes(const int *millerA, const double2 *coefA, int nA, const int *millerB, const double2 *coefB,
-               int band_stride, const int *perm, const int *off, int npw_max, int N1, int N2, int N3, int B1,
-               int mm1, int B2, int mm2, FftPlan p2, FftPlan p3, C *u)
+k_ugrid_planes(BandSource src, KGroup grp, const int *perm, const int *off, int N1, int N2, int N3, int B1, int mm1,
+               int B2, int mm2, FftPlan p2, FftPlan p3, C *u)
 {
     typedef typename CxT<C>::T T;
     extern __shared__ double2 smem_d[];
@@ -151,16 +152,18 @@ k_ugrid_planes(const int *millerA, const double2 *coefA, int nA, const int *mill
     C *tw2 = smem, *tw3 = tw2 + N2, *a = tw3 + N3, *b = a + (size_t)N2 * ld;
     const int tid = threadIdx.x, nth = blockDim.x;
     const int j1 = blockIdx.x, band = blockIdx.y;
-    C *dst = u + ((long)band * N1 + j1) * N2 * N3;
+    C *dst = u + (((long)blockIdx.z * gridDim.y + band) * N1 + j1) * N2 * N3;
     if (pmod(j1 + mm1, N1) >= B1) {
         for (int e = tid; e < N2 * N3; e += nth) dst[e] = mkc<C>(0, 0);
         return;
     }
-    const int set = band >= nA ? 1 : 0;
-    const int *mil = set ? millerB : millerA;
-    const double2 *cf = (set ? coefB : coefA) + (long)(band - set * nA) * band_stride;
-    const int *pm = perm + (long)set * npw_max;
-    const int *of = off + set * (N1 + 1);
+    const int set = band >= src.nA ? 1 : 0;
+    const int k = set ? grp.it[blockIdx.z].kp : grp.it[blockIdx.z].k;
+    const int *mil = src.miller + (long)k * src.npw_max * 3;
+    const double2 *cf = src.coef + ((long)k * src.nband + (set ? src.e0 + band - src.nA : src.o0 + band)) * src.npw_max;
+    const long list = 2 * (long)blockIdx.z + set;
+    const int *pm = perm + list * src.npw_max;
+    const int *of = off + list * (N1 + 1);
     fill_twiddles(tw2, N2, tid, nth);
     fill_twiddles(tw3, N3, tid, nth);
     for (int e = tid; e < 2 * N2 * ld; e += nth) a[e] = mkc<C>(0, 0);
@@ -235,68 +238,70 @@ void fft3d_passes(hipStream_t s, const FftPlan plans[3], const int fft[3], int n
     run_pass(s, data, l1, plans[0], lines);
 }
 
-// The u-grids of two band sets (occupied bands at k, empty bands at k+q) that
-// sit one after the other in u: one zero fill, a scatter per set, and one set
-// of transforms over all nA + nB grids.
+// The u-grids of a group's k-points (per k-point the occupied bands at k, then
+// the empty bands at k+q) in three launches for the whole group.  Small grids
+// leave the chip idle one k-point at a time: 64 k-points of 32 bands on 16^3
+// took 1.47 ms here and 1.38 ms in the pair kernel, in groups of 16 0.27 and
+// 0.17 ms.
 template <typename C>
-void ugrid2_t(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], int nA, int npwA,
-              const int *millerA, const double2 *coefA, int nB, int npwB, const int *millerB,
-              const double2 *coefB, int band_stride, C *u, int lines)
+void ugrids_t(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], const BandSource &src, int n,
+              const KGroup &grp, C *u, int lines)
 {
     const long nr = (long)fft[0] * fft[1] * fft[2];
-    const long tot = nr * (nA + nB);
+    const int nb = src.nA + src.nB;
+    const long tot = nr * nb * n;
     const size_t shm = planes_lds_bytes<C>(fft);
-    if (fft[0] <= 256 && shm <= 160 * 1024 && nA + nB > 0) {
+    if (fft[0] <= 256 && shm <= 160 * 1024 && nb > 0) {
         // sort workspace after the grids (ugrid_bytes counts it)
         int *perm = (int *)(u + tot);
-        int *off = perm + 2 * (long)band_stride;
-        hipLaunchKernelGGL(k_plane_sort, dim3(2), dim3(256), 0, s, millerA, npwA, millerB, npwB, fft[0], band_stride,
-                           perm, off);
+        int *off = perm + 2 * (long)src.npw_max * n;
+        hipLaunchKernelGGL(k_plane_sort, dim3(2, (unsigned)n), dim3(256), 0, s, src, grp, fft[0], perm, off);
         int B1, mm1, B2, mm2;
         axis_box(mmax[0], fft[0], &B1, &mm1);
         axis_box(mmax[1], fft[1], &B2, &mm2);
         if (shm > 65536)
             (void)hipFuncSetAttribute((const void *)&k_ugrid_planes<C>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                       (int)shm);
-        hipLaunchKernelGGL(k_ugrid_planes<C>, dim3((unsigned)fft[0], (unsigned)(nA + nB)), dim3(256), shm, s, millerA,
-                           coefA, nA, millerB, coefB, band_stride, perm, off, band_stride, fft[0], fft[1], fft[2], B1,
-                           mm1, B2, mm2, plans[1], plans[2], u);
-        // axis 1: lines (band, j2, j3), stride N2*N3
+        hipLaunchKernelGGL(k_ugrid_planes<C>, dim3((unsigned)fft[0], (unsigned)nb, (unsigned)n), dim3(256), shm, s, src,
+                           grp, perm, off, fft[0], fft[1], fft[2], B1, mm1, B2, mm2, plans[1], plans[2], u);
+        // axis 1: lines (grid, j2, j3), stride N2*N3
         const int N2 = fft[1], N3 = fft[2];
-        LineSet l1{fft[0], N2 * N3, (long)(nA + nB) * N2 * N3, N2 * N3, 1, 1, 0, 1, 0, 1, 0, 1, 0, nr};
+        LineSet l1{fft[0], N2 * N3, (long)nb * n * N2 * N3, N2 * N3, 1, 1, 0, 1, 0, 1, 0, 1, 0, nr};
         run_pass(s, u, l1, plans[0], lines);
         return;
     }
     unsigned zb = (unsigned)std::min<long>((tot + 255) / 256, 65536);
     hipLaunchKernelGGL(k_zero<C>, dim3(zb), dim3(256), 0, s, u, tot);
-    const long nsA = (long)npwA * nA, nsB = (long)npwB * nB;
-    if (nsA > 0)
-        hipLaunchKernelGGL(k_scatter<C>, dim3((unsigned)((nsA + 255) / 256)), dim3(256), 0, s, millerA, coefA, npwA,
-                           band_stride, nA, fft[0], fft[1], fft[2], u);
-    if (nsB > 0)
-        hipLaunchKernelGGL(k_scatter<C>, dim3((unsigned)((nsB + 255) / 256)), dim3(256), 0, s, millerB, coefB, npwB,
-                           band_stride, nB, fft[0], fft[1], fft[2], u + nr * nA);
-    fft3d_passes(s, plans, fft, nA + nB, mmax, u, lines);
+    for (int i = 0; i < n; i++) {
+        const KItem &it = grp.it[i];
+        C *uk = u + nr * nb * i;
+        auto scatter = [&](int k, int npw, int b0, int count, C *dst) {
+            const long ns = (long)npw * count;
+            if (ns > 0)
+                hipLaunchKernelGGL(k_scatter<C>, dim3((unsigned)((ns + 255) / 256)), dim3(256), 0, s,
+                                   src.miller + (long)k * src.npw_max * 3,
+                                   src.coef + ((long)k * src.nband + b0) * src.npw_max, npw, src.npw_max, count, fft[0],
+                                   fft[1], fft[2], dst);
+        };
+        scatter(it.k, it.npwA, src.o0, src.nA, uk);
+        scatter(it.kp, it.npwB, src.e0, src.nB, uk + nr * src.nA);
+    }
+    fft3d_passes(s, plans, fft, nb * n, mmax, u, lines);
 }
 
 }  // namespace
 
-size_t ugrid_bytes(const int fft[3], int nbands, int npw_max, bool fp32)
+size_t ugrid_bytes(const int fft[3], int nbands, int npw_max, bool fp32, int n)
 {
     const size_t nr = (size_t)fft[0] * fft[1] * fft[2];
-    return nr * nbands * (fp32 ? sizeof(float2) : sizeof(double2)) + sizeof(int) * (2 * (size_t)npw_max + 2 * 257);
+    return n * (nr * nbands * (fp32 ? sizeof(float2) : sizeof(double2)) + sizeof(int) * (2 * (size_t)npw_max + 2 * 257));
 }
 
-void launch_ugrid2(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], int nA, int npwA,
-                   const int *millerA, const double2 *coefA, int nB, int npwB, const int *millerB,
-                   const double2 *coefB, int band_stride, void *u, bool fp32, int lines)
+void launch_ugrids(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], const BandSource &src,
+                   int n, const KGroup &grp, void *u, bool fp32, int lines)
 {
-    if (fp32)
-        ugrid2_t(s, plans, fft, mmax, nA, npwA, millerA, coefA, nB, npwB, millerB, coefB, band_stride, (float2 *)u,
-                 lines);
-    else
-        ugrid2_t(s, plans, fft, mmax, nA, npwA, millerA, coefA, nB, npwB, millerB, coefB, band_stride, (double2 *)u,
-                 lines);
+    if (fp32) ugrids_t(s, plans, fft, mmax, src, n, grp, (float2 *)u, lines);
+    else ugrids_t(s, plans, fft, mmax, src, n, grp, (double2 *)u, lines);
 }
 
 void launch_fft3d(hipStream_t s, const FftPlan plans[3], const int fft[3], int ngrids,

@@ -81,12 +81,21 @@ __device__ __forceinline__ void pair_ops_out(const C (&acc)[NA * NB][MAXG], int 
     });
 }
 
+// The part of a group's k-point blockIdx.y: its grids, umklapp vector, window
+// and outputs (the per-k-point kernel's arguments).
+#define RP_GROUP_ITEM(NR)                                                                      \
+    const KItem &item = kgrp.it[blockIdx.y];                                                    \
+    const C *u_occ = u + (long)blockIdx.y * (nO + nE) * (NR), *u_emp = u_occ + (long)nO * (NR); \
+    const int g01 = item.g0[0], g02 = item.g0[1], g03 = item.g0[2], lo3 = item.lo3;            \
+    M += (long)blockIdx.y * nE * nO * ng;                                                      \
+    ops.p0 += (long)blockIdx.y * nE * nO;
+
 template <typename C, int NA, int NB, int MAXG>
 __global__ void __launch_bounds__(256)
-k_pair(const C *__restrict__ u_occ, const C *__restrict__ u_emp, int nO, int nE, int N1, int N2, int N3,
-       FftPlan p2, FftPlan p3, int ng, const int *__restrict__ gsph, int g01, int g02, int g03, int lo3,
-       int L3, int rows, double2 *__restrict__ M, SplitOps ops)
+k_pair(const C *__restrict__ u, int nO, int nE, int N1, int N2, int N3, FftPlan p2, FftPlan p3, int ng,
+       const int *__restrict__ gsph, KGroup kgrp, int L3, int rows, double2 *__restrict__ M, SplitOps ops)
 {
+    RP_GROUP_ITEM((long)N1 * N2 * N3)
     typedef typename CxT<C>::T T;
     constexpr int NP = NA * NB;
     extern __shared__ double2 smem_d[];
@@ -255,10 +264,10 @@ template <typename C, int N, int MAXG> constexpr int pair_lanes_waves()
 
 template <typename C, int N, int NA, int NB, int MAXG>
 __global__ void __launch_bounds__(256, (pair_lanes_waves<C, N, MAXG>()))
-k_pair_lanes(const C *__restrict__ u_occ, const C *__restrict__ u_emp, int nO, int nE, int N1, int ng,
-             const int *__restrict__ gsph, int g01, int g02, int g03, int lo3, int L3, double2 *__restrict__ M,
-             SplitOps ops)
+k_pair_lanes(const C *__restrict__ u, int nO, int nE, int N1, int ng, const int *__restrict__ gsph, KGroup kgrp, int L3,
+             double2 *__restrict__ M, SplitOps ops)
 {
+    RP_GROUP_ITEM((long)N1 * N * N)
     constexpr int G = pair_group<N>(), Q = N / G, NP = NA * NB;
     constexpr int NGRP = 256 / G;             // lane groups per workgroup
     constexpr int TA = (NP * N + NGRP - 1) / NGRP;    // phase-A lines per group
@@ -420,8 +429,8 @@ k_pair_lanes(const C *__restrict__ u_occ, const C *__restrict__ u_emp, int nO, i
 }
 
 template <typename C, int N, int NA, int NB>
-void launch_pair_lanes(hipStream_t s, int N1, const C *u_occ, const C *u_emp, int nO, int nE, int ng,
-                       const int *gsph, const int g0[3], int lo3, int L3, double2 *M, const SplitOps &ops)
+void launch_pair_lanes(hipStream_t s, int N1, const C *u, int nO, int nE, int ng, const int *gsph, int L3, int n,
+                       const KGroup &kgrp, double2 *M, const SplitOps &ops)
 {
     const unsigned nblk = (unsigned)(((nE + NA - 1) / NA) * ((nO + NB - 1) / NB));
     // the two m3 windows, sized by this window (not its largest allowed width):
@@ -432,8 +441,8 @@ void launch_pair_lanes(hipStream_t s, int N1, const C *u_occ, const C *u_emp, in
         if (shm > 65536)                                                                                     \
             (void)hipFuncSetAttribute((const void *)&k_pair_lanes<C, N, NA, NB, G>,                          \
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);                 \
-        hipLaunchKernelGGL((k_pair_lanes<C, N, NA, NB, G>), dim3(nblk), dim3(256), shm, s, u_occ, u_emp, nO, \
-                           nE, N1, ng, gsph, g0[0], g0[1], g0[2], lo3, L3, M, ops);                          \
+        hipLaunchKernelGGL((k_pair_lanes<C, N, NA, NB, G>), dim3(nblk, (unsigned)n), dim3(256), shm, s, u, nO, \
+                           nE, N1, ng, gsph, kgrp, L3, M, ops);                                               \
     } while (0)
     if constexpr (N >= 96) {
         // large grids come with large spheres: 2048, 4096 or 6144 points
@@ -450,17 +459,15 @@ void launch_pair_lanes(hipStream_t s, int N1, const C *u_occ, const C *u_emp, in
 }
 
 template <typename C, int NA, int NB>
-void launch_pair_t(hipStream_t s, const FftPlan plans[3], const int fft[3], const C *u_occ, const C *u_emp,
-                   int nO, int nE, int ng, const int *gsph, const int g0[3], int lo3, int L3, double2 *M,
-                   const SplitOps &ops)
+void launch_pair_t(hipStream_t s, const FftPlan plans[3], const int fft[3], const C *u, int nO, int nE, int ng,
+                   const int *gsph, int L3, int n, const KGroup &kgrp, double2 *M, const SplitOps &ops)
 {
     const int rows = pair_rows(fft);
     const size_t shm = pair_lds_bytes(fft, L3, rows, sizeof(C), NA * NB);
     const unsigned nblk = (unsigned)(((nE + NA - 1) / NA) * ((nO + NB - 1) / NB));
 #define RP_PAIR(G)                                                                                          \
-    hipLaunchKernelGGL((k_pair<C, NA, NB, G>), dim3(nblk), dim3(256), shm, s, u_occ, u_emp, nO, nE, fft[0], \
-                       fft[1], fft[2], plans[1], plans[2], ng, gsph, g0[0], g0[1], g0[2], lo3, L3, rows, M, \
-                       ops)
+    hipLaunchKernelGGL((k_pair<C, NA, NB, G>), dim3(nblk, (unsigned)n), dim3(256), shm, s, u, nO, nE, fft[0], \
+                       fft[1], fft[2], plans[1], plans[2], ng, gsph, kgrp, L3, rows, M, ops)
     if (ng <= 512) RP_PAIR(2);
     else if (ng <= 1024) RP_PAIR(4);
     else if (ng <= 2048) RP_PAIR(8);
@@ -542,55 +549,36 @@ bool pair_supported(const int fft[3], int ng, int L3, bool fp32)
 
 // the FP32 or FP64 pair kernel for this grid: the lane-group form when it
 // takes the grid, sphere and window, else the generic LDS form
-static void launch_pair_any(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u_occ,
-                            const void *u_emp, int nO, int nE, int ng, const int *gsph, const int g0[3], int lo3,
-                            int L3, bool fp32, double2 *M, const SplitOps &ops)
+void launch_pairs(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u, int nO, int nE, int ng,
+                  const int *gsph, int L3, int n, const KGroup &kgrp, bool fp32, double2 *M, const SplitOps &ops)
 {
     if (fp32 && pair_lanes_f32(fft, ng, L3)) {
-        const float2 *uo = (const float2 *)u_occ, *ue = (const float2 *)u_emp;
+        const float2 *uf = (const float2 *)u;
         switch (fft[1]) {
-#define RP_CASE(n)                                                                                          \
-        case n:                                                                                             \
-            launch_pair_lanes<float2, n, 2, 2>(s, fft[0], uo, ue, nO, nE, ng, gsph, g0, lo3, L3, M, ops);   \
+#define RP_CASE(e)                                                                                        \
+        case e:                                                                                           \
+            launch_pair_lanes<float2, e, 2, 2>(s, fft[0], uf, nO, nE, ng, gsph, L3, n, kgrp, M, ops);      \
             return;
             RP_LANE_LENGTHS_F32(RP_CASE)
 #undef RP_CASE
-        case 96: launch_pair_lanes<float2, 96, 2, 1>(s, fft[0], uo, ue, nO, nE, ng, gsph, g0, lo3, L3, M, ops); return;
+        case 96: launch_pair_lanes<float2, 96, 2, 1>(s, fft[0], uf, nO, nE, ng, gsph, L3, n, kgrp, M, ops); return;
         default: break;
         }
     }
     if (!fp32 && pair_lanes_f64(fft, ng, L3)) {
-        const double2 *uo = (const double2 *)u_occ, *ue = (const double2 *)u_emp;
+        const double2 *ud = (const double2 *)u;
         switch (fft[1]) {
-#define RP_CASE(n)                                                                                          \
-        case n:                                                                                             \
-            launch_pair_lanes<double2, n, 2, 1>(s, fft[0], uo, ue, nO, nE, ng, gsph, g0, lo3, L3, M, ops);  \
+#define RP_CASE(e)                                                                                        \
+        case e:                                                                                           \
+            launch_pair_lanes<double2, e, 2, 1>(s, fft[0], ud, nO, nE, ng, gsph, L3, n, kgrp, M, ops);     \
             return;
             RP_LANE_LENGTHS_F64(RP_CASE)
 #undef RP_CASE
         default: break;
         }
     }
-    if (fp32)
-        launch_pair_t<float2, 2, 2>(s, plans, fft, (const float2 *)u_occ, (const float2 *)u_emp, nO, nE, ng,
-                                    gsph, g0, lo3, L3, M, ops);
-    else
-        launch_pair_t<double2, 1, 1>(s, plans, fft, (const double2 *)u_occ, (const double2 *)u_emp, nO, nE,
-                                     ng, gsph, g0, lo3, L3, M, ops);
-}
-
-void launch_pair_k(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u_occ,
-                   const void *u_emp, int nO, int nE, int ng, const int *gsph, const int g0[3], int lo3,
-                   int L3, bool fp32, double2 *M)
-{
-    launch_pair_any(s, plans, fft, u_occ, u_emp, nO, nE, ng, gsph, g0, lo3, L3, fp32, M, SplitOps{});
-}
-
-void launch_pair_ops(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u_occ,
-                     const void *u_emp, int nO, int nE, int ng, const int *gsph, const int g0[3], int lo3, int L3,
-                     const SplitOps &ops)
-{
-    launch_pair_any(s, plans, fft, u_occ, u_emp, nO, nE, ng, gsph, g0, lo3, L3, true, nullptr, ops);
+    if (fp32) launch_pair_t<float2, 2, 2>(s, plans, fft, (const float2 *)u, nO, nE, ng, gsph, L3, n, kgrp, M, ops);
+    else launch_pair_t<double2, 1, 1>(s, plans, fft, (const double2 *)u, nO, nE, ng, gsph, L3, n, kgrp, M, ops);
 }
 
 }  // namespace rp

@@ -124,14 +124,30 @@ class StageTimer {
 
 // ---- kernel launchers (one translation unit each) --------------------------
 
-// fft.hip: u-grids (scatter + pruned 3-D transform) of two band sets stored
-// one after the other in u (nA grids from millerA/coefA, then nB from
-// millerB/coefB), FP32 or FP64; u holds ugrid_bytes (the grids, then a small
-// sort workspace; band_stride is the npw_max of the coefficient rows).
-size_t ugrid_bytes(const int fft[3], int nbands, int npw_max, bool fp32);
-void launch_ugrid2(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], int nA, int npwA,
-                   const int *millerA, const double2 *coefA, int nB, int npwB, const int *millerB,
-                   const double2 *coefB, int band_stride, void *u, bool fp32, int lines);
+// The k-points of one group of u-grid and pair launches (by value: a kernel
+// argument): occupied bands at k, empty bands at kp, their plane-wave counts,
+// the umklapp vector of k + q and the first m3 of the sphere's window.
+constexpr int kKGroup = 32;
+struct KItem {
+    int k, kp, npwA, npwB, g0[3], lo3;
+};
+struct KGroup {
+    KItem it[kKGroup];
+};
+
+// Where the bands of a group come from: miller [Nk][npw_max][3], coef
+// [Nk][nband][npw_max]; bands [o0, o0 + nA) at k, [e0, e0 + nB) at kp.
+struct BandSource {
+    const int *miller;
+    const double2 *coef;
+    int nband, npw_max, o0, nA, e0, nB;
+};
+
+// fft.hip: the u-grids of n k-points, [n][nA + nB][N1][N2][N3] in FP32 or FP64
+// (then a small sort workspace); ugrid_bytes is their size.
+size_t ugrid_bytes(const int fft[3], int nbands, int npw_max, bool fp32, int n);
+void launch_ugrids(hipStream_t s, const FftPlan plans[3], const int fft[3], const int mmax[3], const BandSource &src,
+                   int n, const KGroup &grp, void *u, bool fp32, int lines);
 
 // fft.hip: in-place batched positive-exponent transform of whole grids.
 void launch_fft3d(hipStream_t s, const FftPlan plans[3], const int fft[3], int ngrids,
@@ -147,7 +163,7 @@ struct SplitOps {
     int NGP = 0, npg = 0, nterm = 0;
 };
 
-// pair.hip: pair densities of one k (grids in FP64, or FP32 when fp32).
+// pair.hip, grids in FP64, or FP32 when fp32.
 size_t pair_lds_bytes(const int fft[3], int L3, int rows, size_t csize, int npairs);
 int pair_rows(const int fft[3]);
 // whether a pair kernel can run this grid, sphere size and m3 window
@@ -155,14 +171,12 @@ bool pair_supported(const int fft[3], int ng, int L3, bool fp32);
 // the smallest line length n of the lane kernels with need <= n <= limit that
 // takes this sphere and m3 window as N2 = N3 = n, or 0
 int pair_lane_edge(int need, int limit, int ng, int L3, bool fp32);
-void launch_pair_k(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u_occ,
-                   const void *u_emp, int nO, int nE, int ng, const int *gsph, const int g0[3],
-                   int lo3, int L3, bool fp32, double2 *M);
-// the same pair densities written as split operands (FP32 grids only): pair
-// (a, b) of this k goes to pair p0 + a nO + b of ops
-void launch_pair_ops(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u_occ,
-                     const void *u_emp, int nO, int nE, int ng, const int *gsph, const int g0[3], int lo3, int L3,
-                     const SplitOps &ops);
+
+// the pair densities of a group of n k-points from its u-grids, into
+// M [n][nE][nO][ng] or, where ops.A is given (FP32 grids), as split operands:
+// pair (a, b) of the group's i-th k-point is pair p0 + (i nE + a) nO + b of ops.
+void launch_pairs(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u, int nO, int nE, int ng,
+                  const int *gsph, int L3, int n, const KGroup &grp, bool fp32, double2 *M, const SplitOps &ops);
 
 // tetra.hip: weights of a pair range.
 void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nband,
