@@ -29,13 +29,13 @@ FLAGS = [
 ]
 
 SOURCES = ["rp_api.cpp", "fft.hip", "pair.hip", "tetra.hip", "chi_f64.hip", "chi_bf16.hip", "head.hip",
-           "screen.hip", "wannier.hip", "qsum.hip", "symmetry.hip"]
+           "screen.hip", "density.hip", "wannier.hip", "qsum.hip", "symmetry.hip"]
 
 
 # FP64 matrix-core kernels that fit two or more waves per SIMD: accumulators in
 # ordinary registers (in AGPRs the compiler moves them all once per loop pass)
 VGPR_MFMA = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-SOURCE_FLAGS = {"chi_f64.hip": VGPR_MFMA}
+SOURCE_FLAGS = {"chi_f64.hip": VGPR_MFMA, "wannier.hip": VGPR_MFMA, "qsum.hip": VGPR_MFMA}
 
 
 def library_path() -> str:

@@ -25,6 +25,8 @@
 // The quadratic forms run as T = eps^-1 conj(P)^T on the FP64 matrix cores
 // (64 x 64 tiles of (G, vector), 16x16x4 FP64 MFMAs), then per vector or per
 // orbital pair a reduction with the densities themselves.
+#include <type_traits>
+
 #include "fft_lds.h"
 
 namespace rp {
@@ -38,18 +40,18 @@ __device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
 }
 
-// Overlap-density grids of vectors v0 .. v0 + nvc - 1 (v = (r nwan + i) nwan
+// Overlap-density grids of the vectors vec[0 .. nvc) (v = (r nwan + i) nwan
 // + j), each times e^{iq.rt}; one thread per (vector, grid point).
 __global__ void k_xdens(int nwan, int N1, int N2, int N3, const double *__restrict__ phi,
-                        const double *__restrict__ centre, const int *__restrict__ R, long v0, int nvc,
+                        const double *__restrict__ centre, const int *__restrict__ R, const int *__restrict__ vec, int nvc,
                         double q1, double q2, double q3, double2 *__restrict__ f)
 {
     const long nr = (long)N1 * N2 * N3;
     const long t = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= nr * nvc) return;
     const long lv = t / nr, p = t - lv * nr;
-    const long v = v0 + lv;
-    const int j = (int)(v % nwan), i = (int)((v / nwan) % nwan), r = (int)(v / ((long)nwan * nwan));
+    const int v = vec[lv];
+    const int j = v % nwan, i = (v / nwan) % nwan, r = v / (nwan * nwan);
     const int p1 = (int)(p / ((long)N2 * N3)), p2 = (int)((p / N3) % N2), p3 = (int)(p % N3);
     const double x[3] = {(double)p1 / N1, (double)p2 / N2, (double)p3 / N3};
     const double qf[3] = {q1, q2, q3};
@@ -73,101 +75,114 @@ __global__ void k_xdens(int nwan, int N1, int N2, int N3, const double *__restri
     f[t] = make_double2(val * c, val * s);
 }
 
-// T = E conj(P)^T over K in [klo, ng) for one frequency (grid z), a 64 x 64
-// tile of (G, vector) per block; E [nfreq][ng][ng], P [nv][ldp].
-// DIAG: out[tile row][f][v] = sum over the tile's rows G in [klo, ng) of
-//       P[v][G] T[G][v];  otherwise out[f][G][v] = T[G][v] (ld nv).
-template <bool DIAG>
-__global__ void __launch_bounds__(256)
-k_wgemm(int ng, int klo, int nv, int nfreq, const double2 *__restrict__ P, long ldp,
-        const double2 *__restrict__ E, double2 *__restrict__ out)
+__device__ __forceinline__ void dma16(const void *src, void *lds)
 {
-    constexpr int KC = 16;
-    __shared__ double2 sE[64][KC + 1];
-    __shared__ double2 sP[KC][64 + 1];
-    __shared__ double2 red[2][64];
+    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
+}
+
+// Quadratic forms of many vectors: per 64 rows G (grid y) and frequency (z),
+//   out[row tile][f][v] = sum_G P[v][G] sum_G' E[f][G][G'] conj(P[v][G'])
+// over G, G' in [klo, ng).  T = E conj(P)^T runs on the FP64 matrix cores, 64
+// rows x 16 CB vectors per workgroup (wave w: 16 rows x all vectors), and its
+// tile is reduced against P at once.  Bound by the matrix cores: two waves per
+// SIMD with the accumulators in ordinary registers, the operands' chunks of 16
+// columns streamed into two LDS buffers (global_load_lds; slot k of row r holds
+// column k ^ (r & 15), so that the 16 rows of an operand read fall on all
+// banks).  2700 vectors, N_G = 1500, 20 frequencies: 25.4 ms at 38.7 TFLOP/s
+// with operands staged through registers and 64 accumulators in AGPRs; 58
+// TFLOP/s here (8.4 ms for the 1355 that need computing).
+template <int CB>
+__global__ void __launch_bounds__(256, 2)
+k_wquad(int ng, int klo, int nv, int nfreq, const double2 *__restrict__ P, long ldp, const double2 *__restrict__ E,
+        double2 *__restrict__ out)
+{
+    constexpr int KC = 16, TC = 16 * CB;
+    __shared__ double2 sE[2][64][KC];
+    __shared__ double2 sP[2][TC][KC];
+    __shared__ double2 red[4][TC];
     const int f = blockIdx.z, tid = threadIdx.x;
-    const int rt0 = blockIdx.y * 64, v0 = blockIdx.x * 64;
+    const int rt0 = blockIdx.y * 64, v0 = blockIdx.x * TC;
     const double2 *Ef = E + (long)f * ng * ng;
     const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
-    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-    d4 accR[2][2], accI[2][2];
+    const int wr = wave * 16;
+    // DMA: a wave-load fills four rows of 16 slots; wave w loads rows 16 w ..
+    // of E and every fourth group of four rows of P
+    auto issue = [&](int stg, int kc) {
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++)
+        for (int t = 0; t < 4; t++) {
+            const int r = wr + 4 * t + lk, k = kc + (li ^ (r & 15));
+            dma16(Ef + (long)min(rt0 + r, ng - 1) * ng + min(k, ng - 1), &sE[stg][wr + 4 * t][0]);
+        }
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++) {
-            accR[rb][cb] = d4{0.0, 0.0, 0.0, 0.0};
-            accI[rb][cb] = d4{0.0, 0.0, 0.0, 0.0};
+        for (int t = 0; t < CB; t++) {
+            const int b = 4 * (wave + 4 * t), r = b + lk, k = kc + (li ^ (r & 15));
+            dma16(P + (long)min(v0 + r, nv - 1) * ldp + min(k, ng - 1), &sP[stg][b][0]);
         }
-    for (int kc = 0; kc < ng; kc += KC) {
-        for (int e = tid; e < 64 * KC; e += 256) {
-            const int rr = e / KC, k = e - rr * KC, i = rt0 + rr, K = kc + k;
-            sE[rr][k] = (i < ng && K < ng && K >= klo) ? Ef[(long)i * ng + K] : make_double2(0.0, 0.0);
-        }
-        for (int e = tid; e < 64 * KC; e += 256) {
-            const int cc = e / KC, k = e - cc * KC, v = v0 + cc, K = kc + k;
-            double2 p = make_double2(0.0, 0.0);
-            if (v < nv && K < ng) p = P[(long)v * ldp + K];
-            sP[k][cc] = make_double2(p.x, -p.y);
-        }
-        __syncthreads();
+    };
+    d4 accR[CB], accI[CB];
+#pragma unroll
+    for (int c = 0; c < CB; c++) {
+        accR[c] = d4{0.0, 0.0, 0.0, 0.0};
+        accI[c] = d4{0.0, 0.0, 0.0, 0.0};
+    }
+    auto work = [&](int stg, int kc, auto edge) {
 #pragma unroll
         for (int k0 = 0; k0 < KC; k0 += 4) {
-            double2 x[2], y[2];
+            const int slot = (k0 + lk) ^ li;
+            double2 x = sE[stg][wr + li][slot], y[CB];
 #pragma unroll
-            for (int rb = 0; rb < 2; rb++) x[rb] = sE[wr + rb * 16 + li][k0 + lk];
+            for (int c = 0; c < CB; c++) y[c] = sP[stg][c * 16 + li][slot];
+            if constexpr (decltype(edge)::value) {
+                const int k = kc + k0 + lk;
+                if (k < klo || k >= ng) {
+                    x = make_double2(0.0, 0.0);
 #pragma unroll
-            for (int cb = 0; cb < 2; cb++) y[cb] = sP[k0 + lk][wc + cb * 16 + li];
-#pragma unroll
-            for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-                for (int cb = 0; cb < 2; cb++) {
-                    accR[rb][cb] = mfma64(x[rb].x, y[cb].x, accR[rb][cb]);
-                    accR[rb][cb] = mfma64(-x[rb].y, y[cb].y, accR[rb][cb]);
-                    accI[rb][cb] = mfma64(x[rb].x, y[cb].y, accI[rb][cb]);
-                    accI[rb][cb] = mfma64(x[rb].y, y[cb].x, accI[rb][cb]);
+                    for (int c = 0; c < CB; c++) y[c] = x;
                 }
+            }
+#pragma unroll
+            for (int c = 0; c < CB; c++) {
+                accR[c] = mfma64(x.x, y[c].x, accR[c]);
+                accI[c] = mfma64(x.y, y[c].x, accI[c]);
+            }
+#pragma unroll
+            for (int c = 0; c < CB; c++) {
+                accR[c] = mfma64(x.y, y[c].y, accR[c]);
+                accI[c] = mfma64(-x.x, y[c].y, accI[c]);
+            }
         }
+    };
+    issue(0, 0);
+    for (int kc = 0, stg = 0; kc < ng; kc += KC, stg ^= 1) {
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
+        if (kc + KC < ng) issue(stg ^ 1, kc + KC);
+        if (kc < klo || kc + KC > ng) work(stg, kc, std::true_type{});
+        else work(stg, kc, std::false_type{});
     }
     // result register r of lane (li, lk) holds row lk + 4 r, column li of a 16x16 block
-    if constexpr (DIAG) {
 #pragma unroll
-        for (int cb = 0; cb < 2; cb++) {
-            const int j = v0 + wc + cb * 16 + li;
-            double2 s = make_double2(0.0, 0.0);
-            if (j < nv) {
+    for (int c = 0; c < CB; c++) {
+        const int j = v0 + c * 16 + li;
+        double2 s = make_double2(0.0, 0.0);
+        if (j < nv) {
 #pragma unroll
-                for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-                    for (int r = 0; r < 4; r++) {
-                        const int i = rt0 + wr + rb * 16 + lk + 4 * r;
-                        if (i >= klo && i < ng)
-                            s = cadd(s, cmul(P[(long)j * ldp + i], make_double2(accR[rb][cb][r], accI[rb][cb][r])));
-                    }
+            for (int r = 0; r < 4; r++) {
+                const int i = rt0 + wr + lk + 4 * r;
+                if (i >= klo && i < ng) s = cadd(s, cmul(P[(long)j * ldp + i], make_double2(accR[c][r], accI[c][r])));
             }
-            // the four lanes of column li (lk = 0..3) hold disjoint rows
-            s.x += __shfl_xor(s.x, 16);
-            s.y += __shfl_xor(s.y, 16);
-            s.x += __shfl_xor(s.x, 32);
-            s.y += __shfl_xor(s.y, 32);
-            if (lk == 0) red[wave >> 1][wc + cb * 16 + li] = s;
         }
-        __syncthreads();
-        if (tid < 64 && v0 + tid < nv)
-            out[((long)blockIdx.y * nfreq + f) * nv + v0 + tid] = cadd(red[0][tid], red[1][tid]);
-    } else {
-#pragma unroll
-        for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-            for (int cb = 0; cb < 2; cb++)
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int i = rt0 + wr + rb * 16 + lk + 4 * r, j = v0 + wc + cb * 16 + li;
-                    if (i < ng && j < nv)
-                        out[((long)f * ng + i) * nv + j] = make_double2(accR[rb][cb][r], accI[rb][cb][r]);
-                }
+        // the four lanes of column li (lk = 0..3) hold disjoint rows
+        s.x += __shfl_xor(s.x, 16);
+        s.y += __shfl_xor(s.y, 16);
+        s.x += __shfl_xor(s.x, 32);
+        s.y += __shfl_xor(s.y, 32);
+        if (lk == 0) red[wave][c * 16 + li] = s;
     }
+    __syncthreads();
+    if (tid < TC && v0 + tid < nv)
+        out[((long)blockIdx.y * nfreq + f) * nv + v0 + tid] =
+            cadd(cadd(red[0][tid], red[1][tid]), cadd(red[2][tid], red[3][tid]));
 }
 
 __device__ __forceinline__ double2 block_sum(double2 s, double2 *red)
@@ -180,19 +195,6 @@ __device__ __forceinline__ double2 block_sum(double2 s, double2 *red)
         __syncthreads();
     }
     return red[0];
-}
-
-// body[f][i][j] = sum_{G in [klo, ng)} P[i][G] T[f][G][j]; block per (i j, f)
-__global__ void __launch_bounds__(256) k_wcross(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp,
-                                                const double2 *__restrict__ T, double2 *__restrict__ body)
-{
-    __shared__ double2 red[256];
-    const int i = blockIdx.x / nwan, j = blockIdx.x % nwan, f = blockIdx.y;
-    double2 s = make_double2(0.0, 0.0);
-    for (int G = klo + threadIdx.x; G < ng; G += 256)
-        s = cadd(s, cmul(P[(long)i * ldp + G], T[((long)f * ng + G) * nwan + j]));
-    s = block_sum(s, red);
-    if (threadIdx.x == 0) body[((long)f * nwan + i) * nwan + j] = s;
 }
 
 // Gram sums of the densities: for output o (pair (a, b) = (o / nb, o % nb),
@@ -251,10 +253,11 @@ __global__ void k_wsum_u(int nfreq, int nR, int nwan, int ng, const int *__restr
     }
 }
 
-// J[f][v], X[v] (+)= pre (...) for the vectors v0 .. v0 + nvc - 1 (one
-// thread per (f, vector)); part [nrt][nfreq][nvc]
-__global__ void k_wsum_x(int nfreq, long nvt, long v0, int nvc, int nrt, int ng, double pre, int head, double avg,
-                         const double2 *__restrict__ E, const double2 *__restrict__ P, long ldp,
+// J[f][v], X[v] (+)= pre (...) for the densities of one pass (one thread per
+// (f, density)): density lv is that of vector vec[lv] and, where
+// vec[nvc + lv] >= 0, of that vector too; part [nrt][nfreq][nvc]
+__global__ void k_wsum_x(int nfreq, long nvt, const int *__restrict__ vec, int nvc, int nrt, int ng, double pre,
+                         int head, double avg, const double2 *__restrict__ E, const double2 *__restrict__ P, long ldp,
                          const double2 *__restrict__ part, const double2 *__restrict__ bare,
                          const double2 *__restrict__ tail, int accumulate, double2 *__restrict__ J,
                          double2 *__restrict__ X)
@@ -267,18 +270,20 @@ __global__ void k_wsum_x(int nfreq, long nvt, long v0, int nvc, int nrt, int ng,
         const double2 n0 = P[(long)lv * ldp];
         hv = avg * (n0.x * n0.x + n0.y * n0.y);
     }
+    const int v = vec[lv], twin = vec[nvc + lv];
+    auto put = [&](double2 *o, double2 x) { *o = accumulate ? cadd(*o, x) : x; };
     if (J) {
         double2 s = tail[lv];
         for (int rt = 0; rt < nrt; rt++) s = cadd(s, part[((long)rt * nfreq + f) * nvc + lv]);
         s = cadd(s, cscale(E[(long)f * ng * ng], hv));
         s = cscale(s, pre);
-        const long o = (long)f * nvt + v0 + lv;
-        J[o] = accumulate ? cadd(J[o], s) : s;
+        put(J + (long)f * nvt + v, s);
+        if (twin >= 0) put(J + (long)f * nvt + twin, s);
     }
     if (X && f == 0) {
         const double2 x = cscale(make_double2(bare[lv].x + hv, bare[lv].y), pre);
-        const long o = v0 + lv;
-        X[o] = accumulate ? cadd(X[o], x) : x;
+        put(X + v, x);
+        if (twin >= 0) put(X + twin, x);
     }
 }
 
@@ -287,33 +292,26 @@ unsigned blocks_for(long n, int per) { return (unsigned)((n + per - 1) / per); }
 }  // namespace
 
 void launch_xdens(hipStream_t s, const Geometry &g, const FftPlan plans[3], int nwan, const double *phi,
-                  const double *centre_dev, const int *R_dev, long v0, int nvc, double2 *grids)
+                  const double *centre_dev, const int *R_dev, const int *vec_dev, int nvc, double2 *grids)
 {
     const long nr = (long)g.fft[0] * g.fft[1] * g.fft[2];
     hipLaunchKernelGGL(k_xdens, dim3(blocks_for(nr * nvc, 256)), dim3(256), 0, s, nwan, g.fft[0], g.fft[1],
-                       g.fft[2], phi, centre_dev, R_dev, v0, nvc, (double)g.iq[0] / g.kmesh[0],
+                       g.fft[2], phi, centre_dev, R_dev, vec_dev, nvc, (double)g.iq[0] / g.kmesh[0],
                        (double)g.iq[1] / g.kmesh[1], (double)g.iq[2] / g.kmesh[2], grids);
     launch_fft3d(s, plans, g.fft, nvc, grids);
 }
 
-int wgemm_row_tiles(int ng) { return (ng + 63) / 64; }
+int wquad_row_tiles(int ng) { return (ng + 63) / 64; }
 
-void launch_wgemm(hipStream_t s, bool diag, int nfreq, int ng, int klo, int nv, const double2 *P, long ldp,
-                  const double2 *E, double2 *out)
+void launch_wquad(hipStream_t s, int nfreq, int ng, int klo, int nv, const double2 *P, long ldp, const double2 *E,
+                  double2 *out)
 {
     if (nv == 0) return;
-    const dim3 grid(blocks_for(nv, 64), (unsigned)wgemm_row_tiles(ng), (unsigned)nfreq);
-    if (diag)
-        hipLaunchKernelGGL(k_wgemm<true>, grid, dim3(256), 0, s, ng, klo, nv, nfreq, P, ldp, E, out);
-    else
-        hipLaunchKernelGGL(k_wgemm<false>, grid, dim3(256), 0, s, ng, klo, nv, nfreq, P, ldp, E, out);
-}
-
-void launch_wcross(hipStream_t s, int nfreq, int nwan, int ng, int klo, const double2 *P, long ldp,
-                   const double2 *T, double2 *body)
-{
-    hipLaunchKernelGGL(k_wcross, dim3((unsigned)(nwan * nwan), (unsigned)nfreq), dim3(256), 0, s, nwan, ng, klo,
-                       P, ldp, T, body);
+    // 80 vectors per workgroup, or 32 where there are no more
+    const int tc = nv <= 32 ? 32 : 80;
+    const dim3 grid(blocks_for(nv, tc), (unsigned)wquad_row_tiles(ng), (unsigned)nfreq);
+    if (tc == 32) hipLaunchKernelGGL(k_wquad<2>, grid, dim3(256), 0, s, ng, klo, nv, nfreq, P, ldp, E, out);
+    else hipLaunchKernelGGL(k_wquad<5>, grid, dim3(256), 0, s, ng, klo, nv, nfreq, P, ldp, E, out);
 }
 
 void launch_wgram(hipStream_t s, int nout, int nb, bool diag, int ng, int klo, int ntail, const double2 *P,
@@ -335,13 +333,13 @@ void launch_wsum_u(hipStream_t s, const Geometry &g, int nfreq, int nR, int nwan
                        (int)head, avg, E, P, ldp, body, bare, tail, accumulate, U, V);
 }
 
-void launch_wsum_x(hipStream_t s, int nfreq, long nvt, long v0, int nvc, int ng, double pre, bool head, double avg,
-                   const double2 *E, const double2 *P, long ldp, const double2 *part, const double2 *bare,
+void launch_wsum_x(hipStream_t s, int nfreq, long nvt, const int *vec_dev, int nvc, int ng, double pre, bool head,
+                   double avg, const double2 *E, const double2 *P, long ldp, const double2 *part, const double2 *bare,
                    const double2 *tail, int accumulate, double2 *J, double2 *X)
 {
     const long n = (long)nfreq * nvc;
-    hipLaunchKernelGGL(k_wsum_x, dim3(blocks_for(n, 128)), dim3(128), 0, s, nfreq, nvt, v0, nvc,
-                       wgemm_row_tiles(ng), ng, pre, (int)head, avg, E, P, ldp, part, bare, tail, accumulate, J, X);
+    hipLaunchKernelGGL(k_wsum_x, dim3(blocks_for(n, 128)), dim3(128), 0, s, nfreq, nvt, vec_dev, nvc,
+                       wquad_row_tiles(ng), ng, pre, (int)head, avg, E, P, ldp, part, bare, tail, accumulate, J, X);
 }
 
 }  // namespace rp

@@ -2,10 +2,12 @@
 // order of launches for each entry point.  All device work goes to the
 // context's stream; nothing here synchronizes except rp_synchronize.
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
 #include <mutex>
 #include <optional>
 #include <unordered_map>
@@ -645,7 +647,7 @@ rp_status rp_destroy(rp_ctx *ctx)
     ctx->spare.clear();
     DevBuf *bufs[] = {&ctx->ugrid, &ctx->ugrid32, &ctx->weights, &ctx->glist, &ctx->freq,  &ctx->kinfo, &ctx->vsqrt,
                       &ctx->work,  &ctx->split_a, &ctx->split_b, &ctx->split_w, &ctx->rho, &ctx->piv,
-                      &ctx->mbuf,  &ctx->bstage,  &ctx->chi_part};
+                      &ctx->mbuf,  &ctx->bstage,  &ctx->chi_part, &ctx->vecs};
     for (hipGraphExec_t e : ctx->batch_execs) (void)hipGraphExecDestroy(e);
     for (DevBuf *b : bufs)
         if (b->p) (void)hipFree(b->p);
@@ -1245,6 +1247,22 @@ rp_status rp_screen_head(rp_ctx *ctx, const rp_cell *cell, int ng, const int *gs
     return check_launch(ctx, "screen head");
 }
 
+// The direct densities of the orbitals at the list's vectors, P [nwan][nlist]
+// (grids: workspace for the route through whole grids, [nwan][N_r], or the
+// lane kernel's density_part).
+static void direct_densities(rp_ctx *ctx, const Geometry &g, const FftPlan plans[3], int nwan, const double *phi,
+                             const double *dcen, int nlist, const int *dgl, const int *hgl, bool zero_ok,
+                             double2 *grids, double2 *P)
+{
+    if (density_lanes(g.fft)) {
+        launch_density(ctx->stream, g, nwan, phi, dcen, nullptr, nullptr, nwan, nlist, dgl, hgl, zero_ok, nlist,
+                       grids, P, ctx->flag);
+        return;
+    }
+    launch_wannier_density(ctx->stream, g, plans, nwan, phi, dcen, grids);
+    launch_wannier_gather(ctx->stream, g, nwan, nlist, dgl, grids, P, ctx->flag, zero_ok);
+}
+
 rp_status rp_wannier_W(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nwan, const double *phi,
                        const double *centre_frac, int ng, const int *gsph, int ntail, const int *gtail,
                        int nfreq, const double *eps_inv, double *Wij)
@@ -1264,31 +1282,29 @@ rp_status rp_wannier_W(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nw
     FftPlan plans[3];
     if ((st = plans3(ctx, g, plans)) != RP_OK) return st;
     const long nr = (long)g.fft[0] * g.fft[1] * g.fft[2];
-    // layout of the Wannier workspace (double2 units):
-    //   grids [nwan][nr] | rho_eps [nwan][ng] | rho_tail [nwan][ntail] | T [nfreq][ng][nwan]
-    const size_t n_grid = (size_t)nwan * nr, n_re = (size_t)nwan * ng, n_rt = (size_t)nwan * ntail;
-    const size_t n_T = (size_t)nfreq * ng * nwan;
-    if ((st = ensure(ctx, ctx->work, sizeof(double2) * (n_grid + n_re + n_rt + n_T))) != RP_OK) return st;
-    // host lists: centres, gsph, gtail packed into one upload
-    std::vector<char> host(sizeof(double) * 3 * nwan + sizeof(int) * 3 * (ng + ntail));
-    std::memcpy(host.data(), centre_frac, sizeof(double) * 3 * nwan);
-    std::memcpy(host.data() + sizeof(double) * 3 * nwan, gsph, sizeof(int) * 3 * ng);
-    if (ntail) std::memcpy(host.data() + sizeof(double) * 3 * nwan + sizeof(int) * 3 * ng, gtail, sizeof(int) * 3 * ntail);
+    // workspace (double2 units): P [nwan][ng + ntail] | part | bare, tail [nwan^2]
+    // | grids [nwan][nr] (where the densities go through whole grids) or their partial sums
+    const long ldp = (long)ng + ntail;
+    const size_t n2 = (size_t)nwan * nwan, n_p = (size_t)nwan * ldp, n_part = wbody_part(nfreq, nwan, ng);
+    const size_t n_grid = density_lanes(g.fft) ? density_part(g.fft, nwan, (int)ldp) : (size_t)nwan * nr;
+    if ((st = ensure(ctx, ctx->work, sizeof(double2) * (n_p + n_part + 2 * n2 + n_grid))) !=
+        RP_OK)
+        return st;
+    double2 *P = (double2 *)ctx->work.p, *part = P + n_p, *bare = part + n_part, *tail = bare + n2, *grids = tail + n2;
+    // host lists: centres, gsph + gtail packed into one upload
+    const size_t hc = sizeof(double) * 3 * nwan;
+    std::vector<char> host(hc + sizeof(int) * 3 * ldp);
+    std::memcpy(host.data(), centre_frac, hc);
+    std::memcpy(host.data() + hc, gsph, sizeof(int) * 3 * ng);
+    if (ntail) std::memcpy(host.data() + hc + sizeof(int) * 3 * ng, gtail, sizeof(int) * 3 * ntail);
     if ((st = upload(ctx, ctx->kinfo, host.data(), host.size())) != RP_OK) return st;
     const double *dcen = (const double *)ctx->kinfo.p;
-    const int *dgs = (const int *)((const char *)ctx->kinfo.p + sizeof(double) * 3 * nwan);
-    const int *dgt = dgs + 3 * ng;
-    double2 *grids = (double2 *)ctx->work.p;
-    double2 *rho_e = grids + n_grid;
-    double2 *rho_t = rho_e + n_re;
-    double2 *T = rho_t + n_rt;
+    const int *dgl = (const int *)((const char *)ctx->kinfo.p + hc);
     StageTimer t(ctx, RP_STAGE_WANNIER);
-    launch_wannier_density(ctx->stream, g, plans, nwan, phi, dcen, grids);
-    launch_wannier_gather(ctx->stream, g, nwan, ng, dgs, grids, rho_e, ctx->flag);
-    launch_wannier_gather(ctx->stream, g, nwan, ntail, dgt, grids, rho_t, ctx->flag);
+    direct_densities(ctx, g, plans, nwan, phi, dcen, (int)ldp, dgl, (const int *)(host.data() + hc), false, grids, P);
+    launch_wgram(ctx->stream, (int)n2, nwan, false, ng, 0, ntail, P, ldp, bare, tail);
     const double pre = kHartreeEv * 4.0 * kPi / (g.volume * g.nk);
-    launch_wannier_W(ctx->stream, nfreq, nwan, ng, rho_e, ntail, rho_t, (const double2 *)eps_inv, pre, T,
-                     (double2 *)Wij);
+    launch_wbody(ctx->stream, nfreq, nwan, ng, 0, P, ldp, (const double2 *)eps_inv, tail, pre, part, (double2 *)Wij);
     return check_launch(ctx, "wannier projection");
 }
 
@@ -1549,6 +1565,56 @@ rp_status rp_coulomb_cell_average(const rp_cell *cell, double *avg)
     return RP_OK;
 }
 
+// The exchange vectors v = (r, i, j) to compute, each with a twin or -1.  The
+// overlap density of (-R, j, i) is that of (R, i, j) moved by -R: the same up to
+// a phase, so that both have the same J and X, and a list that holds R and -R
+// needs half of the densities.  The image and the cut that a grid point gets
+// agree between the two except where rounding decides, at the points nearest
+// the midpoint's and the orbitals' half-cell boundaries; these are evaluated,
+// and a pair that differs there is computed both ways.
+static void exchange_vectors(const Geometry &g, int nwan, const double *cen, int nR, const int *R,
+                             std::vector<int> &vec, std::vector<int> &twin)
+{
+    std::map<std::array<int, 3>, int> at;
+    for (int r = nR - 1; r >= 0; r--) at[{R[3 * r], R[3 * r + 1], R[3 * r + 2]}] = r;
+    auto image = [](double x, double ci, double cj, double Ra, bool &in) {
+        const double m = 0.5 * (ci + cj + Ra);
+        double d = x - m;
+        d -= std::floor(d + 0.5);
+        const double rt = m + d, di = rt - ci, dj = rt - Ra - cj;
+        in = di >= -0.5 && di < 0.5 && dj >= -0.5 && dj < 0.5;
+        return std::nearbyint(rt - x);
+    };
+    auto alike = [&](int i, int j, const int *Rv) {
+        for (int a = 0; a < 3; a++) {
+            const double ci = cen[3 * i + a], cj = cen[3 * j + a], Ra = (double)Rv[a];
+            const int N = g.fft[a];
+            for (double c : {0.5 * (ci + cj + Ra), ci, cj}) {
+                const double p = std::nearbyint((c + 0.5) * N), x = (p - N * std::floor(p / N)) / N;
+                bool in, tin;
+                if (image(x, ci, cj, Ra, in) != image(x, cj, ci, -Ra, tin) + Ra || in != tin) return false;
+            }
+        }
+        return true;
+    };
+    std::vector<char> done((size_t)nR * nwan * nwan, 0);
+    for (int r = 0; r < nR; r++) {
+        const int *Rv = R + 3 * r;
+        const auto m = at.find({-Rv[0], -Rv[1], -Rv[2]});
+        for (int i = 0; i < nwan; i++)
+            for (int j = 0; j < nwan; j++) {
+                const int v = (r * nwan + i) * nwan + j;
+                if (done[v]) continue;
+                int t = m == at.end() ? -1 : (m->second * nwan + j) * nwan + i;
+                if (t == v || (t >= 0 && (done[t] || !alike(i, j, Rv)))) t = -1;
+                done[v] = 1;
+                if (t >= 0) done[t] = 1;
+                vec.push_back(v);
+                twin.push_back(t);
+            }
+    }
+}
+
 rp_status rp_wannier_qterm(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nwan, const double *phi,
                            const double *centre_frac, int nR, const int *R, int ng, const int *gsph, int ntail,
                            const int *gtail, int nfreq, const double *eps_inv, int accumulate, double *U,
@@ -1582,15 +1648,19 @@ rp_status rp_wannier_qterm(rp_ctx *ctx, const rp_cell *cell, const int iq[3], in
     const long nr = (long)g.fft[0] * g.fft[1] * g.fft[2];
     const long ldp = (long)ng + ntail;
     const long nvt = (long)nR * nwan * nwan;
-    // exchange densities per pass: grids of about 512 MB at most
-    const long nvc = std::max(1L, std::min({512L, nvt, (512L << 20) / (nr * (long)sizeof(double2))}));
-    const long nrt = wgemm_row_tiles(ng);
+    // exchange densities per pass: whole grids of about 512 MB at most, or
+    // densities of about 256 MB
+    const bool lanes = density_lanes(g.fft);
+    const long cap = lanes ? std::min(1280L, std::max(80L, (256L << 20) / (ldp * (long)sizeof(double2)) / 80 * 80))
+                           : std::max(1L, std::min(512L, (512L << 20) / (nr * (long)sizeof(double2))));
+    const long nvc = std::min(cap, nvt);
+    const long nrt = wquad_row_tiles(ng);
     // workspace (double2 units):
-    //   grids [max(nvc, nwan)][nr] | PU [nwan][ldp] | PJ [nvc][ldp] | TU [nfreq][ng][nwan]
-    //   | part [nrt][nfreq][nvc] | bodyU [nfreq][nwan^2] | bareU, tailU [nwan^2] | bareJ, tailJ [nvc]
+    //   grids [max(nvc, nwan)][nr] (for the lane kernel: its partial sums, at most one per CU) | PU [nwan][ldp] | PJ [nvc][ldp]
+    //   | partU | part [nrt][nfreq][nvc] | bodyU [nfreq][nwan^2] | bareU, tailU [nwan^2] | bareJ, tailJ [nvc]
     const size_t n2 = (size_t)nwan * nwan;
-    const size_t sz[] = {(size_t)std::max<long>(nvc, nwan) * nr, (size_t)nwan * ldp, (size_t)nvc * ldp,
-                         (size_t)nfreq * ng * nwan, (size_t)nrt * nfreq * nvc, (size_t)nfreq * n2, n2, n2,
+    const size_t sz[] = {lanes ? 256 * (size_t)ldp : (size_t)std::max<long>(nvc, nwan) * nr, (size_t)nwan * ldp, (size_t)nvc * ldp,
+                         wbody_part(nfreq, nwan, ng), (size_t)nrt * nfreq * nvc, (size_t)nfreq * n2, n2, n2,
                          (size_t)nvc, (size_t)nvc};
     size_t tot = 0;
     for (size_t x : sz) tot += x;
@@ -1598,7 +1668,7 @@ rp_status rp_wannier_qterm(rp_ctx *ctx, const rp_cell *cell, const int iq[3], in
     double2 *bufs[10];
     bufs[0] = (double2 *)ctx->work.p;
     for (int b = 1; b < 10; b++) bufs[b] = bufs[b - 1] + sz[b - 1];
-    double2 *grids = bufs[0], *PU = bufs[1], *PJ = bufs[2], *TU = bufs[3], *part = bufs[4], *bodyU = bufs[5];
+    double2 *grids = bufs[0], *PU = bufs[1], *PJ = bufs[2], *partU = bufs[3], *part = bufs[4], *bodyU = bufs[5];
     double2 *bareU = bufs[6], *tailU = bufs[7], *bareJ = bufs[8], *tailJ = bufs[9];
     // host lists: centres | gsph + gtail | R, packed into one upload
     const size_t hc = sizeof(double) * 3 * nwan, hg = sizeof(int) * 3 * ldp, hr = sizeof(int) * 3 * nR;
@@ -1610,6 +1680,7 @@ rp_status rp_wannier_qterm(rp_ctx *ctx, const rp_cell *cell, const int iq[3], in
     if ((st = upload(ctx, ctx->kinfo, host.data(), host.size())) != RP_OK) return st;
     const double *dcen = (const double *)ctx->kinfo.p;
     const int *dgl = (const int *)((const char *)ctx->kinfo.p + hc);
+    const int *hgl = (const int *)(host.data() + hc);
     const int *dR = (const int *)((const char *)ctx->kinfo.p + hc + hg);
     const double pre = kHartreeEv * 4.0 * kPi / (g.volume * g.nk);
     const double avg = head ? cell_average(g) : 0.0;
@@ -1618,24 +1689,39 @@ rp_status rp_wannier_qterm(rp_ctx *ctx, const rp_cell *cell, const int iq[3], in
     hipStream_t s = ctx->stream;
     StageTimer t(ctx, RP_STAGE_WANNIER);
     if (U || V) {
-        launch_wannier_density(s, g, plans, nwan, phi, dcen, grids);
-        launch_wannier_gather(s, g, nwan, (int)ldp, dgl, grids, PU, ctx->flag, head);
-        if (U) {
-            launch_wgemm(s, false, nfreq, ng, klo, nwan, PU, ldp, E, TU);
-            launch_wcross(s, nfreq, nwan, ng, klo, PU, ldp, TU, bodyU);
-        }
+        direct_densities(ctx, g, plans, nwan, phi, dcen, (int)ldp, dgl, hgl, head, grids, PU);
+        if (U) launch_wbody(s, nfreq, nwan, ng, klo, PU, ldp, E, nullptr, 1.0, partU, bodyU);
         launch_wgram(s, (int)n2, nwan, false, ng, klo, ntail, PU, ldp, bareU, tailU);
         launch_wsum_u(s, g, nfreq, nR, nwan, ng, dR, pre, head, avg, E, PU, ldp, bodyU, bareU, tailU, accumulate,
                       (double2 *)U, (double2 *)V);
     }
     if (J || X) {
-        for (long v0 = 0; v0 < nvt; v0 += nvc) {
-            const int n = (int)std::min(nvc, nvt - v0);
-            launch_xdens(s, g, plans, nwan, phi, dcen, dR, v0, n, grids);
-            launch_wannier_gather(s, g, n, (int)ldp, dgl, grids, PJ, ctx->flag, head);
-            if (J) launch_wgemm(s, true, nfreq, ng, klo, n, PJ, ldp, E, part);
+        // each pass's vectors, then their twins
+        std::vector<int> vec, twin;
+        exchange_vectors(g, nwan, centre_frac, nR, R, vec, twin);
+        const long nu = (long)vec.size(), npass = (nu + nvc - 1) / nvc;
+        const long per = lanes ? std::min(nvc, ((nu + npass - 1) / npass + 79) / 80 * 80) : nvc;
+        std::vector<int> lists;
+        lists.reserve(2 * nu);
+        for (long v0 = 0; v0 < nu; v0 += per) {
+            const long n = std::min(per, nu - v0);
+            lists.insert(lists.end(), vec.begin() + v0, vec.begin() + v0 + n);
+            lists.insert(lists.end(), twin.begin() + v0, twin.begin() + v0 + n);
+        }
+        if ((st = upload(ctx, ctx->vecs, lists.data(), sizeof(int) * lists.size())) != RP_OK) return st;
+        for (long v0 = 0; v0 < nu; v0 += per) {
+            const int n = (int)std::min(per, nu - v0);
+            const int *dv = (const int *)ctx->vecs.p + 2 * v0;
+            if (lanes) {
+                launch_density(s, g, nwan, phi, dcen, dR, dv, n, (int)ldp, dgl, hgl, head, ldp, grids, PJ,
+                               ctx->flag);
+            } else {
+                launch_xdens(s, g, plans, nwan, phi, dcen, dR, dv, n, grids);
+                launch_wannier_gather(s, g, n, (int)ldp, dgl, grids, PJ, ctx->flag, head);
+            }
+            if (J) launch_wquad(s, nfreq, ng, klo, n, PJ, ldp, E, part);
             launch_wgram(s, n, 0, true, ng, klo, ntail, PJ, ldp, bareJ, tailJ);
-            launch_wsum_x(s, nfreq, nvt, v0, n, ng, pre, head, avg, E, PJ, ldp, part, bareJ, tailJ, accumulate,
+            launch_wsum_x(s, nfreq, nvt, dv, n, ng, pre, head, avg, E, PJ, ldp, part, bareJ, tailJ, accumulate,
                           (double2 *)J, (double2 *)X);
         }
     }

@@ -72,6 +72,7 @@ struct rp_ctx {
     rp::DevBuf piv;                 // pivots
     rp::DevBuf mbuf;                // pair densities of one k batch (batch entry point)
     rp::DevBuf bstage;              // device copies of a batch's G and frequency lists
+    rp::DevBuf vecs;                // exchange vectors of a q-term and their twins
     // the last batch's graphs (launched in order) and the launch arguments
     // they were captured with; batch_nodes counts their kernel nodes
     std::vector<hipGraphExec_t> batch_execs;
@@ -252,9 +253,20 @@ void launch_wannier_density(hipStream_t s, const Geometry &g, const FftPlan plan
 void launch_wannier_gather(hipStream_t s, const Geometry &g, int nwan, int nlist,
                            const int *glist, const double2 *fgrid, double2 *rho, int *flag,
                            bool zero_ok = false);
-void launch_wannier_W(hipStream_t s, int nfreq, int nwan, int ng, const double2 *rho_eps,
-                      int ntail, const double2 *rho_tail, const double2 *einv, double pre,
-                      double2 *T, double2 *Wij);
+// out[f][i][j] = pre (sum_{G,G' in [klo, ng)} P[i][G] eps^-1[f][G][G'] conj(P[j][G'])
+// + tail[i][j]) (tail may be NULL); part holds wbody_part values
+size_t wbody_part(int nfreq, int nwan, int ng);
+void launch_wbody(hipStream_t s, int nfreq, int nwan, int ng, int klo, const double2 *P, long ldp, const double2 *einv,
+                  const double2 *tail, double pre, double2 *part, double2 *out);
+
+// density.hip: direct (R_dev, vec_dev NULL: nv orbitals) or exchange densities
+// rho_v at the vectors of a list into P [nv][ldp], on the grids it takes
+// (part: density_part values)
+bool density_lanes(const int fft[3]);
+size_t density_part(const int fft[3], int nv, int nlist);
+void launch_density(hipStream_t s, const Geometry &g, int nwan, const double *phi, const double *centre_dev,
+                    const int *R_dev, const int *vec_dev, int nv, int nlist, const int *glist_dev,
+                    const int *glist_host, bool zero_ok, long ldp, double2 *part, double2 *P, int *flag);
 
 // symmetry.hip: unfolding of coefficients and of G-indexed matrices
 void launch_unfold_coef(hipStream_t s, int nband, int npw, const int *idx, const int *miller, const int delta[3],
@@ -264,19 +276,17 @@ void launch_unfold_matrix(hipStream_t s, int nfreq, int ng, int ng_src, const in
 
 // qsum.hip: one q-point's term of the q-sums of U, V, J, X
 void launch_xdens(hipStream_t s, const Geometry &g, const FftPlan plans[3], int nwan, const double *phi,
-                  const double *centre_dev, const int *R_dev, long v0, int nvc, double2 *grids);
-int wgemm_row_tiles(int ng);
-void launch_wgemm(hipStream_t s, bool diag, int nfreq, int ng, int klo, int nv, const double2 *P, long ldp,
-                  const double2 *E, double2 *out);
-void launch_wcross(hipStream_t s, int nfreq, int nwan, int ng, int klo, const double2 *P, long ldp,
-                   const double2 *T, double2 *body);
+                  const double *centre_dev, const int *R_dev, const int *vec_dev, int nvc, double2 *grids);
+int wquad_row_tiles(int ng);
+void launch_wquad(hipStream_t s, int nfreq, int ng, int klo, int nv, const double2 *P, long ldp, const double2 *E,
+                  double2 *out);
 void launch_wgram(hipStream_t s, int nout, int nb, bool diag, int ng, int klo, int ntail, const double2 *P,
                   long ldp, double2 *bare, double2 *tail);
 void launch_wsum_u(hipStream_t s, const Geometry &g, int nfreq, int nR, int nwan, int ng, const int *R_dev,
                    double pre, bool head, double avg, const double2 *E, const double2 *P, long ldp,
                    const double2 *body, const double2 *bare, const double2 *tail, int accumulate, double2 *U,
                    double2 *V);
-void launch_wsum_x(hipStream_t s, int nfreq, long nvt, long v0, int nvc, int ng, double pre, bool head, double avg,
+void launch_wsum_x(hipStream_t s, int nfreq, long nvt, const int *vec_dev, int nvc, int ng, double pre, bool head, double avg,
                    const double2 *E, const double2 *P, long ldp, const double2 *part, const double2 *bare,
                    const double2 *tail, int accumulate, double2 *J, double2 *X);
 

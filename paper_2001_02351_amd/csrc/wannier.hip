@@ -62,49 +62,139 @@ __global__ void k_wgather(int nwan, int N1, int N2, int N3, int nlist, const int
     }
 }
 
-// T[f][G][j] = sum_G' eps^-1[f][G][G'] conj(rho_j(G')); one block per (G, f)
-__global__ void __launch_bounds__(256) k_wproj1(int nwan, int ng, const double2 *rho, const double2 *einv,
-                                                double2 *T)
+constexpr int kBodyRows = 32;   // rows of eps^-1 per workgroup of k_wbody
+
+typedef double d4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
 {
-    extern __shared__ double2 red[];  // [256][nwan]
-    const int G = blockIdx.x, f = blockIdx.y, tid = threadIdx.x;
-    const double2 *row = einv + ((long)f * ng + G) * ng;
-    for (int j = 0; j < nwan; j++) red[tid * nwan + j] = make_double2(0.0, 0.0);
-    for (int h = tid; h < ng; h += 256) {
-        const double2 e = row[h];
-        for (int j = 0; j < nwan; j++) {
-            const double2 r = rho[(long)j * ng + h];
-            // e * conj(r)
-            red[tid * nwan + j].x += e.x * r.x + e.y * r.y;
-            red[tid * nwan + j].y += e.y * r.x - e.x * r.y;
-        }
-    }
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if (tid < s)
-            for (int j = 0; j < nwan; j++) red[tid * nwan + j] = cadd(red[tid * nwan + j], red[(tid + s) * nwan + j]);
-        __syncthreads();
-    }
-    if (tid < nwan) T[((long)f * ng + G) * nwan + tid] = red[tid];
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
 }
 
-// W[f][i][j] = pre (sum_G rho_i(G) T[f][G][j] + sum_tail rho_i conj(rho_j)); one block per (i,j,f)
-__global__ void __launch_bounds__(256) k_wproj2(int nwan, int ng, const double2 *rho, int ntail,
-                                                const double2 *rtail, const double2 *T, double pre,
-                                                double2 *W)
+// Quadratic forms of all orbital pairs: over the rows of one workgroup,
+//   part[f][row block][i][j] = sum_G P[i][G] sum_G' eps^-1[f][G][G'] conj(P[j][G'])
+// with G, G' in [klo, ng).  Bound by reading eps^-1 once.  A workgroup owns 32
+// rows G, each of its four waves a quarter of the columns G', so that enough
+// loads are in flight: the four lanes of a row read 64 contiguous bytes of it
+// (and of their orbital) straight into a matrix operand; 16 NC orbitals.  The product with P over the rows follows in LDS.
+// 20 x 1500^2, ten orbitals: 0.62 ms with one workgroup per row and a reduction
+// through LDS per orbital, 0.20 here (3.6 TB/s).
+template <int NC, int RB>
+__global__ void __launch_bounds__(256, 2)
+k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, const double2 *__restrict__ einv,
+        double2 *__restrict__ part)
 {
-    __shared__ double2 red[256];
-    const int i = blockIdx.x / nwan, j = blockIdx.x % nwan, f = blockIdx.y, tid = threadIdx.x;
-    double2 s = make_double2(0.0, 0.0);
-    for (int G = tid; G < ng; G += 256) s = cadd(s, cmul(rho[(long)i * ng + G], T[((long)f * ng + G) * nwan + j]));
-    for (int G = tid; G < ntail; G += 256) s = cadd(s, cmulc(rtail[(long)j * ntail + G], rtail[(long)i * ntail + G]));
-    red[tid] = s;
-    __syncthreads();
-    for (int h = 128; h > 0; h >>= 1) {
-        if (tid < h) red[tid] = cadd(red[tid], red[tid + h]);
-        __syncthreads();
+    constexpr int LD = 16 * NC + 1;
+    __shared__ double2 sT[4][16 * RB][LD];
+    const int f = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int r0 = blockIdx.x * 16 * RB;
+    const double2 *E = einv + (long)f * ng * ng;
+    const int steps = (ng + 15) / 16, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+    const double2 *row[RB];
+    const double2 *orb[NC];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++) row[rb] = E + (long)min(r0 + rb * 16 + li, ng - 1) * ng;
+#pragma unroll
+    for (int c = 0; c < NC; c++) orb[c] = P + (long)min(c * 16 + li, nwan - 1) * ldp;
+    d4 accR[RB][NC], accI[RB][NC];
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+        for (int c = 0; c < NC; c++) {
+            accR[rb][c] = d4{0.0, 0.0, 0.0, 0.0};
+            accI[rb][c] = d4{0.0, 0.0, 0.0, 0.0};
+        }
+    double2 e[RB][4], o[NC][4];
+    auto load = [&](int st) {
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            const int k = st * 16 + 4 * q + lk;
+            const bool in = k >= klo && k < ng;
+            const int kc = min(k, ng - 1);
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++) {
+                const double2 v = row[rb][kc];
+                e[rb][q] = in ? v : make_double2(0.0, 0.0);
+            }
+#pragma unroll
+            for (int c = 0; c < NC; c++) {
+                const double2 v = orb[c][kc];
+                o[c][q] = in ? v : make_double2(0.0, 0.0);
+            }
+        }
+    };
+    if (s0 < s1) load(s0);
+    for (int st = s0; st < s1; st++) {
+        double2 x[RB][4], y[NC][4];
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++) x[rb][q] = e[rb][q];
+#pragma unroll
+            for (int c = 0; c < NC; c++) y[c][q] = o[c][q];
+        }
+        if (st + 1 < s1) load(st + 1);
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                for (int c = 0; c < NC; c++) {
+                    accR[rb][c] = mfma64(x[rb][q].x, y[c][q].x, accR[rb][c]);
+                    accI[rb][c] = mfma64(x[rb][q].y, y[c][q].x, accI[rb][c]);
+                }
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                for (int c = 0; c < NC; c++) {
+                    accR[rb][c] = mfma64(x[rb][q].y, y[c][q].y, accR[rb][c]);
+                    accI[rb][c] = mfma64(-x[rb][q].x, y[c][q].y, accI[rb][c]);
+                }
+        }
     }
-    if (tid == 0) W[((long)f * nwan + i) * nwan + j] = cscale(red[0], pre);
+    // result register r of lane (li, lk) holds row lk + 4 r, column li of a 16x16 block
+#pragma unroll
+    for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+        for (int c = 0; c < NC; c++)
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+                sT[wave][rb * 16 + lk + 4 * r][c * 16 + li] = make_double2(accR[rb][c][r], accI[rb][c][r]);
+    __syncthreads();
+    for (int t = tid; t < 256 * RB * NC; t += 256) {
+        const int r = t / (16 * NC), c = t % (16 * NC);
+        sT[0][r][c] = cadd(cadd(sT[0][r][c], sT[1][r][c]), cadd(sT[2][r][c], sT[3][r][c]));
+    }
+    __syncthreads();
+    for (int t = tid; t < nwan * nwan; t += 256) {
+        const int i = t / nwan, j = t - i * nwan;
+        double2 s = make_double2(0.0, 0.0);
+        for (int r = 0; r < 16 * RB; r++) {
+            const int G = r0 + r;
+            if (G >= klo && G < ng) s = cadd(s, cmul(P[(long)i * ldp + G], sT[0][r][j]));
+        }
+        part[((long)f * gridDim.x + blockIdx.x) * nwan * nwan + t] = s;
+    }
+}
+
+// out[f][ij] = pre (sum of the row blocks' parts + tail[ij]), one wave per
+// (ij, f): the lanes take row blocks in turn
+__global__ void __launch_bounds__(256)
+k_wbody_sum(int n2, int nfreq, int nblk, const double2 *__restrict__ part, const double2 *__restrict__ tail, double pre,
+            double2 *__restrict__ out)
+{
+    const long t = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (t >= (long)n2 * nfreq) return;
+    const int f = (int)(t / n2), ij = (int)(t - (long)f * n2);
+    double2 s = make_double2(0.0, 0.0);
+    for (int b = lane; b < nblk; b += 64) s = cadd(s, part[((long)f * nblk + b) * n2 + ij]);
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        s.x += __shfl_xor(s.x, o);
+        s.y += __shfl_xor(s.y, o);
+    }
+    if (lane == 0) out[t] = cscale(tail ? cadd(s, tail[ij]) : s, pre);
 }
 
 }  // namespace
@@ -132,13 +222,17 @@ void launch_wannier_gather(hipStream_t s, const Geometry &g, int nwan, int nlist
                        (int)zero_ok);
 }
 
-void launch_wannier_W(hipStream_t s, int nfreq, int nwan, int ng, const double2 *rho_eps, int ntail,
-                      const double2 *rho_tail, const double2 *einv, double pre, double2 *T, double2 *Wij)
+size_t wbody_part(int nfreq, int nwan, int ng) { return (size_t)nfreq * ((ng + kBodyRows - 1) / kBodyRows) * nwan * nwan; }
+
+void launch_wbody(hipStream_t s, int nfreq, int nwan, int ng, int klo, const double2 *P, long ldp, const double2 *einv,
+                  const double2 *tail, double pre, double2 *part, double2 *out)
 {
-    const size_t shm = sizeof(double2) * 256 * (size_t)nwan;
-    hipLaunchKernelGGL(k_wproj1, dim3(ng, nfreq), dim3(256), shm, s, nwan, ng, rho_eps, einv, T);
-    hipLaunchKernelGGL(k_wproj2, dim3(nwan * nwan, nfreq), dim3(256), 0, s, nwan, ng, rho_eps, ntail,
-                       rho_tail, T, pre, Wij);
+    const dim3 grid((unsigned)((ng + kBodyRows - 1) / kBodyRows), (unsigned)nfreq);
+    if (nwan <= 16) hipLaunchKernelGGL((k_wbody<1, kBodyRows / 16>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
+    else hipLaunchKernelGGL((k_wbody<2, kBodyRows / 16>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
+    const long n = (long)nwan * nwan * nfreq;
+    hipLaunchKernelGGL(k_wbody_sum, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, nwan * nwan, nfreq, (int)grid.x,
+                       part, tail, pre, out);
 }
 
 }  // namespace rp
