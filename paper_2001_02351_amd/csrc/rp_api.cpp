@@ -171,11 +171,53 @@ static rp_status plans3(rp_ctx *ctx, const Geometry &g, FftPlan plans[3])
     return RP_OK;
 }
 
+// A copy of host data in the context's pinned ring, or nullptr where there is
+// no ring, the data are too large for it, or the stream is being captured (a
+// captured copy reads its source when the graph runs, which must then be the
+// caller's own memory).
+static const void *pinned_copy(rp_ctx *ctx, const void *host, size_t bytes)
+{
+    if (bytes > rp_ctx::kPinSeg) return nullptr;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ctx->stream, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone) {
+        (void)hipGetLastError();
+        return nullptr;
+    }
+    if (!ctx->pin_tried) {
+        ctx->pin_tried = true;
+        bool ok = hipHostMalloc((void **)&ctx->pin, rp_ctx::kPinSegs * rp_ctx::kPinSeg, 0) == hipSuccess;
+        if (!ok) ctx->pin = nullptr;
+        for (int i = 0; ok && i < rp_ctx::kPinSegs; i++)
+            ok = hipEventCreateWithFlags(&ctx->pin_ev[i], hipEventDisableTiming) == hipSuccess;
+        if (!ok) {
+            (void)hipGetLastError();
+            if (ctx->pin) (void)hipHostFree(ctx->pin);
+            ctx->pin = nullptr;
+        }
+    }
+    if (!ctx->pin) return nullptr;
+    if (ctx->pin_off + bytes > rp_ctx::kPinSeg) {
+        const int next = (ctx->pin_seg + 1) % rp_ctx::kPinSegs;
+        if (hipEventRecord(ctx->pin_ev[ctx->pin_seg], ctx->stream) != hipSuccess) return nullptr;
+        ctx->pin_left[ctx->pin_seg] = true;
+        // the copies out of the segment to be reused (eight segments ago)
+        if (ctx->pin_left[next] && hipEventSynchronize(ctx->pin_ev[next]) != hipSuccess) return nullptr;
+        ctx->pin_left[next] = false;
+        ctx->pin_seg = next;
+        ctx->pin_off = 0;
+    }
+    char *p = ctx->pin + ctx->pin_seg * rp_ctx::kPinSeg + ctx->pin_off;
+    std::memcpy(p, host, bytes);
+    ctx->pin_off += (bytes + 255) / 256 * 256;
+    return p;
+}
+
 static rp_status upload(rp_ctx *ctx, DevBuf &b, const void *host, size_t bytes)
 {
     rp_status st = ensure(ctx, b, bytes);
-    if (st != RP_OK) return st;
-    if (bytes && hipMemcpyAsync(b.p, host, bytes, hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
+    if (st != RP_OK || !bytes) return st;
+    const void *pinned = pinned_copy(ctx, host, bytes);
+    if (hipMemcpyAsync(b.p, pinned ? pinned : host, bytes, hipMemcpyHostToDevice, ctx->stream) != hipSuccess)
         return fail(ctx, RP_E_DEVICE, "host-to-device copy failed");
     return RP_OK;
 }
@@ -652,6 +694,9 @@ rp_status rp_destroy(rp_ctx *ctx)
     for (DevBuf *b : bufs)
         if (b->p) (void)hipFree(b->p);
     if (ctx->flag) (void)hipFree(ctx->flag);
+    for (hipEvent_t e : ctx->pin_ev)
+        if (e) (void)hipEventDestroy(e);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     if (ctx->own_stream) (void)hipStreamDestroy(ctx->stream);
     delete ctx;
     return RP_OK;
@@ -1459,19 +1504,44 @@ static inline long long miller_key(int a, int b, int c)
 static rp_status op_source_index(rp_ctx *ctx, const int W[9], const int delta[3], int nfrom, const int *from, int nto,
                                  const int *to, std::vector<int> &src_idx)
 {
-    std::unordered_map<long long, int> where;
-    where.reserve((size_t)nfrom * 2);
-    for (int i = 0; i < nfrom; i++) where.emplace(miller_key(from[3 * i], from[3 * i + 1], from[3 * i + 2]), i);
     src_idx.resize(nto);
+    // positions by Miller index: a table over the box of `from` where that is
+    // at most a few dozen times the list (a sphere fills half of its box), else a map
+    int lo[3], hi[3];
+    for (int a = 0; a < 3; a++) {
+        lo[a] = hi[a] = from[a];
+        for (int i = 1; i < nfrom; i++) {
+            lo[a] = std::min(lo[a], from[3 * i + a]);
+            hi[a] = std::max(hi[a], from[3 * i + a]);
+        }
+    }
+    const double box = ((double)hi[0] - lo[0] + 1) * ((double)hi[1] - lo[1] + 1) * ((double)hi[2] - lo[2] + 1);
+    const bool dense = box <= 32.0 * nfrom + 4096.0;
+    std::vector<int> table;
+    std::unordered_map<long long, int> where;
+    const int n1 = dense ? hi[1] - lo[1] + 1 : 0, n2 = dense ? hi[2] - lo[2] + 1 : 0;
+    if (dense) {
+        table.assign((size_t)box, -1);
+        for (int i = nfrom - 1; i >= 0; i--)   // the first of equal vectors counts
+            table[((size_t)(from[3 * i] - lo[0]) * n1 + (from[3 * i + 1] - lo[1])) * n2 + (from[3 * i + 2] - lo[2])] = i;
+    } else {
+        where.reserve((size_t)nfrom * 2);
+        for (int i = 0; i < nfrom; i++) where.emplace(miller_key(from[3 * i], from[3 * i + 1], from[3 * i + 2]), i);
+    }
     for (int g = 0; g < nto; g++) {
         const int v[3] = {to[3 * g] + delta[0], to[3 * g + 1] + delta[1], to[3 * g + 2] + delta[2]};
-        int m[3];
+        int m[3], at = -1;
         for (int a = 0; a < 3; a++) m[a] = W[a] * v[0] + W[3 + a] * v[1] + W[6 + a] * v[2];   // (W^T v)_a
-        const auto it = where.find(miller_key(m[0], m[1], m[2]));
-        if (it == where.end())
+        if (!dense) {
+            const auto it = where.find(miller_key(m[0], m[1], m[2]));
+            if (it != where.end()) at = it->second;
+        } else if (m[0] >= lo[0] && m[0] <= hi[0] && m[1] >= lo[1] && m[1] <= hi[1] && m[2] >= lo[2] && m[2] <= hi[2]) {
+            at = table[((size_t)(m[0] - lo[0]) * n1 + (m[1] - lo[1])) * n2 + (m[2] - lo[2])];
+        }
+        if (at < 0)
             return fail(ctx, RP_E_RANGE, "target vector %d (%d %d %d) has no source vector", g, to[3 * g],
                         to[3 * g + 1], to[3 * g + 2]);
-        src_idx[g] = it->second;
+        src_idx[g] = at;
     }
     return RP_OK;
 }

@@ -73,6 +73,18 @@ struct rp_ctx {
     rp::DevBuf mbuf;                // pair densities of one k batch (batch entry point)
     rp::DevBuf bstage;              // device copies of a batch's G and frequency lists
     rp::DevBuf vecs;                // exchange vectors of a q-term and their twins
+    // Pinned staging of the small host lists (index lists, frequencies): copies
+    // from it are queued, where a copy from ordinary memory waits for the
+    // stream's earlier work.  A ring of segments; an event marks the copies out
+    // of a segment that the ring has left.
+    static constexpr int kPinSegs = 8;
+    static constexpr size_t kPinSeg = (size_t)512 << 10;
+    char *pin = nullptr;
+    bool pin_tried = false;
+    int pin_seg = 0;
+    size_t pin_off = 0;
+    hipEvent_t pin_ev[kPinSegs] = {};
+    bool pin_left[kPinSegs] = {};
     // the last batch's graphs (launched in order) and the launch arguments
     // they were captured with; batch_nodes counts their kernel nodes
     std::vector<hipGraphExec_t> batch_execs;
