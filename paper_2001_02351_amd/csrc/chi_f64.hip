@@ -8,7 +8,7 @@
 // with a = w_p M_p(G) and b = M_p(G').
 //
 // Tiling: a 256-thread block owns 64 rows G and 16 CB columns G' (CB = 2, 3, 4
-// or 5) for NW = 1 or 2 frequencies; wave w owns 16 of the rows and all the
+// or 5) for two frequencies (the last block one, where they are odd); wave w owns 16 of the rows and all the
 // columns, so that each weighted row value feeds CB column blocks.  What
 // bounds it is the FP64 matrix-core rate: back-to-back 16x16x4 ops with their
 // accumulators in ordinary registers reach 77.3 TFLOP/s on this card, and
@@ -18,7 +18,7 @@
 // compiled with the accumulators in ordinary registers.  (A 64 x 64 tile for
 // four frequencies on one wave per SIMD kept its 256 accumulators in AGPRs
 // and moved all of them to and fro once per chunk: 48.8 TFLOP/s on 16 000
-// pairs at N_G = 1500 and 20 frequencies, now 60.1; 59.6 of the Hermitian half.)
+// pairs at N_G = 1500 and 20 frequencies, now 65.0; 59.6 of the Hermitian half.)
 //
 // The pair dimension is consumed in chunks of 16 pairs staged through LDS with
 // two buffers: while the matrix cores work on one chunk, the next chunk's rows
@@ -32,6 +32,8 @@
 // 12 288 pairs at N_G = 89 and 10 frequencies (16^3 grid, run_q) went from
 // 13.95 to 6.84 ms with it, one of 27 648 at N_G = 300 and 16 (24^3, q -> 0)
 // from 23.7 to 13.2 ms.
+#include <type_traits>
+
 #include "fft_lds.h"
 
 namespace rp {
@@ -73,12 +75,12 @@ __device__ __forceinline__ void tile_of(int id, int nct, int tc, int herm, int &
 // the elements on and above the diagonal are stored, each with its mirror
 // image.  nslice > 1: slice y of the chunks goes to out + y * nfreq * ng^2
 // (no mirror, no accumulation), else into chi = out.
-template <int NW, int CB>
+template <int CB>
 __global__ void __launch_bounds__(256, 2)
-k_chi_f64(long npair, int ng, const double2 *__restrict__ M, int nfreq, int fbase, const double2 *__restrict__ w,
+k_chi_f64(long npair, int ng, const double2 *__restrict__ M, int nfreq, const double2 *__restrict__ w,
           int accumulate, int herm, int nslice, double2 *__restrict__ out)
 {
-    constexpr int TC = 16 * CB;
+    constexpr int NW = 2, TC = 16 * CB;
     // [stage][pair][64 rows], [stage][pair][TC columns], then [stage][NW][pair] weights
     __shared__ double2 sA[2][kKC][kT];
     __shared__ double2 sB[2][kKC][TC];
@@ -90,7 +92,7 @@ k_chi_f64(long npair, int ng, const double2 *__restrict__ M, int nfreq, int fbas
     tile_of(blockIdx.x, (ng + TC - 1) / TC, TC, herm, rt, ct);
     const int rt0 = rt * kT, ct0 = ct * TC;
     const int wr = wave * 16;
-    const int f0 = fbase + blockIdx.z * NW;
+    const int f0 = blockIdx.z * NW;
     const long nchunk = (npair + kKC - 1) / kKC;
     const long c0 = nchunk * blockIdx.y / nslice, c1 = nchunk * (blockIdx.y + 1) / nslice;
     const bool live = rt0 + wr < ng;   // a wave whose rows all lie past the end only moves data
@@ -134,47 +136,52 @@ k_chi_f64(long npair, int ng, const double2 *__restrict__ M, int nfreq, int fbas
         const double2 w0 = wload(c0);
         if (tid < NW * kKC) sw[0][wiw][wpp] = w0;
     }
-    for (long c = c0; c < c1; c++) {
-        const int stg = (int)((c - c0) & 1);
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        double2 wnext = make_double2(0.0, 0.0);
-        if (c + 1 < c1) {
-            issue(stg ^ 1, c + 1);
-            wnext = wload(c + 1);
-        }
-        if (live) {
-#pragma unroll
-            for (int s = 0; s < kKC / 4; s++) {
-                const int pp = 4 * s + lk;
-                const double2 av = sA[stg][pp][wr + li];
-                double2 bv[CB];
-#pragma unroll
-                for (int cb = 0; cb < CB; cb++) bv[cb] = sB[stg][pp][cb * 16 + li];
-                double2 a[NW];
-#pragma unroll
-                for (int iw = 0; iw < NW; iw++) a[iw] = cmul(av, sw[stg][iw][pp]);
-                // first halves of the four products for all accumulators, then the
-                // second halves: dependent matrix-core ops are 2 NW CB instructions apart
-#pragma unroll
-                for (int iw = 0; iw < NW; iw++)
-#pragma unroll
-                    for (int cb = 0; cb < CB; cb++) {
-                        accR[iw][cb] = mfma64(a[iw].x, bv[cb].x, accR[iw][cb]);
-                        accI[iw][cb] = mfma64(a[iw].y, bv[cb].x, accI[iw][cb]);
-                    }
-#pragma unroll
-                for (int iw = 0; iw < NW; iw++)
-#pragma unroll
-                    for (int cb = 0; cb < CB; cb++) {
-                        accR[iw][cb] = mfma64(a[iw].y, bv[cb].y, accR[iw][cb]);
-                        accI[iw][cb] = mfma64(-a[iw].x, bv[cb].y, accI[iw][cb]);
-                    }
+    auto chunks = [&](auto freqs) {
+        constexpr int NF = decltype(freqs)::value;
+        for (long c = c0; c < c1; c++) {
+            const int stg = (int)((c - c0) & 1);
+            __builtin_amdgcn_s_waitcnt(0);
+            __syncthreads();
+            double2 wnext = make_double2(0.0, 0.0);
+            if (c + 1 < c1) {
+                issue(stg ^ 1, c + 1);
+                wnext = wload(c + 1);
             }
+            if (live) {
+#pragma unroll
+                for (int s = 0; s < kKC / 4; s++) {
+                    const int pp = 4 * s + lk;
+                    const double2 av = sA[stg][pp][wr + li];
+                    double2 bv[CB];
+#pragma unroll
+                    for (int cb = 0; cb < CB; cb++) bv[cb] = sB[stg][pp][cb * 16 + li];
+                    double2 a[NF];
+#pragma unroll
+                    for (int iw = 0; iw < NF; iw++) a[iw] = cmul(av, sw[stg][iw][pp]);
+                    // first halves of the four products for all accumulators, then the
+                    // second halves: dependent matrix-core ops are 2 NF CB instructions apart
+#pragma unroll
+                    for (int iw = 0; iw < NF; iw++)
+#pragma unroll
+                        for (int cb = 0; cb < CB; cb++) {
+                            accR[iw][cb] = mfma64(a[iw].x, bv[cb].x, accR[iw][cb]);
+                            accI[iw][cb] = mfma64(a[iw].y, bv[cb].x, accI[iw][cb]);
+                        }
+#pragma unroll
+                    for (int iw = 0; iw < NF; iw++)
+#pragma unroll
+                        for (int cb = 0; cb < CB; cb++) {
+                            accR[iw][cb] = mfma64(a[iw].y, bv[cb].y, accR[iw][cb]);
+                            accI[iw][cb] = mfma64(-a[iw].x, bv[cb].y, accI[iw][cb]);
+                        }
+                }
+            }
+            // the other stage's weights: its readers finished before this chunk's barrier
+            if (c + 1 < c1 && tid < NW * kKC) sw[stg ^ 1][wiw][wpp] = wnext;
         }
-        // the other stage's weights: its readers finished before this chunk's barrier
-        if (c + 1 < c1 && tid < NW * kKC) sw[stg ^ 1][wiw][wpp] = wnext;
-    }
+    };
+    if (f0 + 1 < nfreq) chunks(std::integral_constant<int, 2>{});
+    else chunks(std::integral_constant<int, 1>{});
 
     // result register r of lane (li, lk) holds row lk + 4 r, column li of a 16x16 block
     const long n2 = (long)ng * ng;
@@ -238,26 +245,29 @@ unsigned f64_tiles(int ng, int cb, bool herm)
     return n;
 }
 
-// cb: the width that pads N_G least (the wider on a tie: fewer weight
-// products per matrix op).  nslice: the chip holds 512 workgroups (two per
-// CU); a launch of u tiles x frequency groups takes ceil(u s / 512) rounds of
-// nchunk / s chunks, plus about six chunks' time per round to fill and store,
-// plus the partial tiles written and read (about 0.0075 chunk times each).
-// The s of least cost is taken, with at least eight chunks per slice and the
-// partial chi within part_max bytes.
+// cb: the least time for the tiles formed, at the rates measured for each
+// width (TFLOP/s executed on 16 000 pairs, N_G = 1500, 20 frequencies: 62, 64,
+// 66 and 67 for 2, 3, 4 and 5 column blocks: the weight products and row reads
+// are shared by more).  nslice: the chip holds 512 workgroups (two per CU); u
+// tiles x frequency pairs take ceil(u s / 512) rounds of nchunk / s chunks,
+// plus about six chunks' time per round to fill and store, plus the partial
+// tiles written and read (about 0.0075 chunk times each).  The s of least cost
+// is taken, with at least eight chunks per slice and the partial chi within
+// part_max bytes.
 F64Shape f64_shape(long npair, int ng, int nfreq, bool herm, size_t part_max)
 {
     F64Shape best;
-    int width = 1 << 30;
+    constexpr double rate[] = {62.0, 64.0, 66.0, 67.0};
+    double least = 1e300;
     for (int cb = 5; cb >= 2; cb--) {
-        const int w = (ng + 16 * cb - 1) / (16 * cb) * cb;
-        if (w < width) {
-            width = w;
+        const double t = (double)f64_tiles(ng, cb, herm) * cb / rate[cb - 2];
+        if (t < least) {
+            least = t;
             best.cb = cb;
         }
     }
     best.tiles = f64_tiles(ng, best.cb, herm);
-    const double u = (double)best.tiles * ((nfreq + 1) / 2);
+    const double u = 0.5 * best.tiles * nfreq;
     const long nchunk = (npair + kKC - 1) / kKC;
     double cost = 1e300;
     for (int s = 1; s <= 64 && (s == 1 || nchunk / s >= 8); s++) {
@@ -269,21 +279,6 @@ F64Shape f64_shape(long npair, int ng, int nfreq, bool herm, size_t part_max)
         }
     }
     return best;
-}
-
-template <int NW>
-void launch_tiles(hipStream_t s, const F64Shape &sh, int groups, int fbase, long npair, int ng, const double2 *M,
-                  int nfreq, const double2 *w, int accumulate, int herm, double2 *out)
-{
-    const dim3 grid(sh.tiles, (unsigned)sh.nslice, (unsigned)groups);
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, npair, ng, M, nfreq, fbase, w, accumulate, herm, sh.nslice,
-                           out);
-    };
-    if (sh.cb == 5) go(k_chi_f64<NW, 5>);
-    else if (sh.cb == 4) go(k_chi_f64<NW, 4>);
-    else if (sh.cb == 3) go(k_chi_f64<NW, 3>);
-    else go(k_chi_f64<NW, 2>);
 }
 
 }  // namespace
@@ -299,11 +294,14 @@ void launch_chi_f64(hipStream_t s, long npair, int ng, const double2 *M, int nfr
 {
     const F64Shape sh = f64_shape(npair, ng, nfreq, herm, part_max);
     double2 *out = sh.nslice > 1 ? (double2 *)part : chi;
-    // frequencies in pairs; an odd last one by itself
-    if (nfreq / 2)
-        launch_tiles<2>(s, sh, nfreq / 2, 0, npair, ng, M, nfreq, w, accumulate, (int)herm, out);
-    if (nfreq % 2)
-        launch_tiles<1>(s, sh, 1, nfreq - 1, npair, ng, M, nfreq, w, accumulate, (int)herm, out);
+    const dim3 grid(sh.tiles, (unsigned)sh.nslice, (unsigned)((nfreq + 1) / 2));
+    auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, npair, ng, M, nfreq, w, accumulate, (int)herm, sh.nslice, out);
+    };
+    if (sh.cb == 5) go(k_chi_f64<5>);
+    else if (sh.cb == 4) go(k_chi_f64<4>);
+    else if (sh.cb == 3) go(k_chi_f64<3>);
+    else go(k_chi_f64<2>);
     if (sh.nslice > 1) {
         const long n = (long)nfreq * ng * ng;
         hipLaunchKernelGGL(k_chi_f64_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ng, nfreq, sh.nslice,
