@@ -26,6 +26,8 @@
 // kPivotFloor (a condition number beyond ~1e13, where an FP64 inverse has no
 // correct digits left) is reported as singular; a non-finite pivot as a
 // non-finite input.
+#include <cmath>
+
 #include "fft_lds.h"
 
 namespace rp {
@@ -396,115 +398,142 @@ k_gj_inner(int ng, int c0, int nb, int cs, int wc, double2 *pb, const double2 *r
             }
 }
 
+typedef unsigned int u4 __attribute__((ext_vector_type(4)));
+
+// `bytes` from p on: past them a buffer load gives zeros and a store does
+// nothing.  The whole offset goes into the checked vector part (the scalar
+// offset would be taken off the size first, and wrap).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t window(const double2 *p, long bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(unsigned)min(bytes, 0xffffffffL), 0x00020000);
+}
+
+__device__ __forceinline__ double2 load16(__amdgpu_buffer_rsrc_t r, int v)
+{
+    return __builtin_bit_cast(double2, __builtin_amdgcn_raw_buffer_load_b128(r, v, 0, 0));
+}
+
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, int v, double2 x)
+{
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u4, x), r, v, 0, 0);
+}
+
 // Update of the columns outside panel [c0, c0 + nb) (see the header), P in pb:
 //   A[i][j] = sum_k pb[k][i] rk[k][j] + (i outside the panel rows ? A[i][j] : 0)
-// A 256-thread block owns a 64x64 tile of one matrix; each wave a 32x32
-// sub-tile (2x2 blocks of 16x16) on v_mfma_f64_16x16x4f64 (A operand lane
-// i + 16k, B operand lane j + 16k, result register r of lane l at row
-// l / 16 + 4 r, column l % 16).  The tiles of the next panel's columns go to
-// its buffer pbn instead of A, those of this panel's columns copy it back.
-__global__ void __launch_bounds__(256, 3)
-k_gj_update(int ng, int c0, int nb, double2 *a, const double2 *pb, double2 *pbn, const double2 *rk)
+// A 256-thread block owns 64 columns and `run` tiles of 64 rows of one matrix:
+// the 64 pivot rows of its columns stay in LDS (64 KB, two blocks per CU), and
+// wave w takes rows 16 w .. + 15 of each tile (4 blocks of 16x16) on
+// v_mfma_f64_16x16x4f64 (A operand lane i + 16k, B operand lane j + 16k,
+// result register r of lane l at row l / 16 + 4 r, column l % 16).  The waves
+// run without barriers: each reads its own panel rows straight into the
+// operand layout four steps ahead and, in a tile's first steps, the old values
+// it will add.  The tiles of the next panel's columns go to its buffer pbn
+// instead of A, those of this panel's columns copy it back.
+// Bound by the matrix cores with gaps: 20 matrices of 1500, 64 columns: 418 us
+// = 53 TFLOP/s and 3.4 TB/s of A (542 us while 32x32 sub-tiles of a wave read
+// both operands from chunks in LDS between barriers; 470 us with this form on
+// plain loads, whose 64-bit addresses cost the instructions that the bounded
+// buffer loads' 32-bit offsets save; without any memory traffic 386 us); 4
+// matrices of 6000: 1.28 ms (1.56 ms).
+__global__ void __launch_bounds__(256, 2)
+k_gj_update(int ng, int c0, int nb, int run, double2 *a, const double2 *pb, double2 *pbn, const double2 *rk)
 {
-    // the panel's 64 columns pass through LDS in chunks of 16, so that a CU
-    // holds several workgroups and one's loads overlap another's matrix work;
-    // the registers are held to three waves per SIMD (three workgroups per
-    // CU; four would spill)
-    constexpr int KC = 16;
-    __shared__ double2 sP[KC][64 + 1];
-    __shared__ double2 sR[KC][64];
+    constexpr int KC = 16, D = 4, STEPS = kGjNb / 4, NT = 256;
+    __shared__ double2 sR[kGjNb * 64];
     const int f = blockIdx.z, tid = threadIdx.x;
-    const int rt0 = blockIdx.y * 64, ct0 = blockIdx.x * 64;
+    const int rt0 = blockIdx.y * run * 64, rt1 = min(ng, rt0 + run * 64), ct0 = blockIdx.x * 64;
     double2 *A = a + (long)f * ng * ng;
     const double2 *B = pb + (long)f * kGjNb * ng;
     if (ct0 == c0) {
-        for (int k0 = 0; k0 < nb; k0 += KC) {
-            for (int e = tid; e < KC * 64; e += 256) {
-                const int k = e >> 6, r = e & 63;
-                if (rt0 + r < ng && k0 + k < nb) sP[k][r] = B[(long)(k0 + k) * ng + rt0 + r];
+        for (int r0 = rt0; r0 < rt1; r0 += 64)
+            for (int k0 = 0; k0 < nb; k0 += KC) {
+                for (int e = tid; e < KC * 64; e += NT) {
+                    const int k = e >> 6, r = e & 63;
+                    if (r0 + r < ng && k0 + k < nb) sR[k * 65 + r] = B[(long)(k0 + k) * ng + r0 + r];
+                }
+                __syncthreads();
+                for (int e = tid; e < KC * 64; e += NT) {
+                    const int r = e / KC, k = e % KC;
+                    if (r0 + r < ng && k0 + k < nb) A[(long)(r0 + r) * ng + c0 + k0 + k] = sR[k * 65 + r];
+                }
+                __syncthreads();
             }
-            __syncthreads();
-            for (int e = tid; e < KC * 64; e += 256) {
-                const int r = e / KC, k = e % KC;
-                if (rt0 + r < ng && k0 + k < nb) A[(long)(rt0 + r) * ng + c0 + k0 + k] = sP[k][r];
-            }
-            __syncthreads();
-        }
         return;
     }
-    const double2 *R = rk + (long)f * kGjNb * ng;
-    const int wave = tid >> 6, lane = tid & 63, li = lane & 15, lk = lane >> 4;
-    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-    d4 accR[2][2], accI[2][2];
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const auto rB = window(B, (long)nb * ng * 16);
+    const auto rR = window(rk + (long)f * kGjNb * ng, (long)nb * ng * 16);
+    // of rows or columns past ng these are other elements, not used
+    const int vp = (lk * ng + li) * 16;
+    auto fetch = [&](int i0, int ks) { return load16(rB, vp + (4 * ks * ng + i0) * 16); };
+    double2 p[D];
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++)
+    for (int d = 0; d < D; d++) p[d] = fetch(rt0 + wave * 16, d);
+    {
+        double2 t[kGjNb * 64 / NT];
 #pragma unroll
-        for (int bc = 0; bc < 2; bc++) {
-            accR[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
-            accI[rb][bc] = d4{0.0, 0.0, 0.0, 0.0};
-        }
-    // each thread moves 4 panel and 4 pivot-row elements of a chunk; the next
-    // chunk's are loaded into registers before the current chunk's matrix
-    // work, so their latency is covered by it
-    constexpr int PER = 64 * KC / 256;
-    double2 pp[PER], pr[PER];
-    auto fetch = [&](int kc) {
+        for (int q = 0; q < kGjNb * 64 / NT; q++) t[q] = load16(rR, (tid & 63) * 16 + ((q * (NT / 64) + wave) * ng + ct0) * 16);
 #pragma unroll
-        for (int q = 0; q < PER; q++) {
-            const int e = tid + q * 256, k = e >> 6, x = e & 63;
-            pp[q] = kc + k < nb && rt0 + x < ng ? B[(long)(kc + k) * ng + rt0 + x] : make_double2(0.0, 0.0);
-            pr[q] = kc + k < nb && ct0 + x < ng ? R[(long)(kc + k) * ng + ct0 + x] : make_double2(0.0, 0.0);
-        }
-    };
-    fetch(0);
-    for (int kc = 0; kc < nb; kc += KC) {
-#pragma unroll
-        for (int q = 0; q < PER; q++) {
-            const int e = tid + q * 256;
-            sP[e >> 6][e & 63] = pp[q];
-            sR[e >> 6][e & 63] = pr[q];
-        }
-        __syncthreads();
-        if (kc + KC < nb) fetch(kc + KC);
-#pragma unroll
-        for (int k0 = 0; k0 < KC; k0 += 4) {
-            double2 x[2], y[2];
-#pragma unroll
-            for (int rb = 0; rb < 2; rb++) x[rb] = sP[k0 + lk][wr + rb * 16 + li];
-#pragma unroll
-            for (int bc = 0; bc < 2; bc++) y[bc] = sR[k0 + lk][wc + bc * 16 + li];
-#pragma unroll
-            for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-                for (int bc = 0; bc < 2; bc++) {
-                    accR[rb][bc] = mfma64(x[rb].x, y[bc].x, accR[rb][bc]);
-                    accI[rb][bc] = mfma64(x[rb].x, y[bc].y, accI[rb][bc]);
-                }
-#pragma unroll
-            for (int rb = 0; rb < 2; rb++)
-#pragma unroll
-                for (int bc = 0; bc < 2; bc++) {
-                    accR[rb][bc] = mfma64(-x[rb].y, y[bc].y, accR[rb][bc]);
-                    accI[rb][bc] = mfma64(x[rb].y, y[bc].x, accI[rb][bc]);
-                }
-        }
-        __syncthreads();
+        for (int q = 0; q < kGjNb * 64 / NT; q++) sR[tid + q * NT] = t[q];
     }
+    __syncthreads();
     const bool next = ct0 == c0 + kGjNb;
     double2 *N = pbn + (long)f * kGjNb * ng;
+    // the next step's rows of sR are read before a step's matrix work
+    double2 yn[4];
 #pragma unroll
-    for (int rb = 0; rb < 2; rb++)
+    for (int bc = 0; bc < 4; bc++) yn[bc] = sR[lk * 64 + bc * 16 + li];
+    for (int i0 = rt0 + wave * 16; i0 < rt1; i0 += NT / 4) {
+        const auto rA = window(A + (long)i0 * ng + ct0, ((long)(ng - i0) * ng - ct0) * 16);
+        d4 accR[4], accI[4];
+        double2 old[4][4];
+        auto prev = [&](int e) { old[e % 4][e / 4] = load16(rA, vp + (e / 4 * 4 * ng + e % 4 * 16) * 16); };
 #pragma unroll
-        for (int bc = 0; bc < 2; bc++)
+        for (int bc = 0; bc < 4; bc++) {
+            accR[bc] = d4{0.0, 0.0, 0.0, 0.0};
+            accI[bc] = d4{0.0, 0.0, 0.0, 0.0};
+        }
 #pragma unroll
-            for (int r = 0; r < 4; r++) {
-                const int i = rt0 + wr + rb * 16 + lk + 4 * r, j = ct0 + wc + bc * 16 + li;
-                if (i >= ng || j >= ng) continue;
-                double2 v = make_double2(accR[rb][bc][r], accI[rb][bc][r]);
-                if (i < c0 || i >= c0 + nb) v = cadd(v, A[(long)i * ng + j]);
-                if (next) N[(long)(j - ct0) * ng + i] = v;
-                else A[(long)i * ng + j] = v;
+        for (int ks = 0; ks < STEPS; ks++) {
+            const double2 x = p[ks % D];
+            p[ks % D] = ks + D < STEPS ? fetch(i0, ks + D) : fetch(i0 + NT / 4, ks + D - STEPS);
+            if (ks < 8) {
+                prev(2 * ks);
+                prev(2 * ks + 1);
             }
+            double2 y[4];
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) {
+                y[bc] = yn[bc];
+                yn[bc] = sR[(4 * ((ks + 1) % STEPS) + lk) * 64 + bc * 16 + li];
+            }
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) accR[bc] = mfma64(x.x, y[bc].x, accR[bc]);
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) accI[bc] = mfma64(x.x, y[bc].y, accI[bc]);
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) accR[bc] = mfma64(-x.y, y[bc].y, accR[bc]);
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) accI[bc] = mfma64(x.y, y[bc].x, accI[bc]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const bool keep = i0 < c0 || i0 >= c0 + kGjNb;
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int i = i0 + lk + 4 * r;
+#pragma unroll
+            for (int bc = 0; bc < 4; bc++) {
+                const int x = bc * 16 + li;
+                double2 v = make_double2(accR[bc][r], accI[bc][r]);
+                if (keep) v = cadd(v, old[bc][r]);
+                if (next) {
+                    if (i < ng && ct0 + x < ng) N[(long)x * ng + i] = v;
+                } else if (ct0 + x < ng) {
+                    store16(rA, vp + (r * 4 * ng + bc * 16) * 16, v);
+                }
+            }
+        }
+    }
 }
 
 // undo the row swaps as column swaps in reverse order; one thread per row
@@ -561,6 +590,23 @@ size_t invert_scratch_bytes(int ng, int nfreq)
     return sizeof(double2) * (size_t)kGjNb * (3 * ng + 16) * nfreq;
 }
 
+// Row tiles per workgroup of the update.  A CU's time is about 7 us per tile
+// (its matrix work) and 6 us per round of its two workgroups (the pivot rows'
+// latency): 8 matrices of 777, 1 .. 4 tiles: model 53, 54, 48, 62 us (and a
+// constant), measured 69.9 (2), 62.9 (3), 74.5 (4).  Large grids hardly differ
+// (1500 x 20: 418, 420, 425 us for 2, 3, 4; 6000 x 4: 1280, 1296, 1261).
+static int update_run(int nfreq, int t)
+{
+    int best = 1;
+    double least = 0.0;
+    for (int run = 1; run <= 4; run++) {
+        const double blocks = (double)nfreq * std::max(t - 1, 1) * ((t + run - 1) / run);
+        const double n = std::ceil(blocks / 256.0), cost = 7.0 * n * run + 6.0 * std::ceil(n / 2.0);
+        if (run == 1 || cost < least) best = run, least = cost;
+    }
+    return best;
+}
+
 template <int R, int W, int NT>
 static void panel_steps(hipStream_t s, int nfreq, int ng, int c0, int nb, double2 *pb, double2 *rkp, int *piv,
                         int *flag)
@@ -579,13 +625,15 @@ void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratc
     const unsigned t = (unsigned)((ng + 63) / 64);
     const size_t panel = (size_t)kGjNb * ng * nfreq;
     double2 *pb = scratch, *pbn = scratch + panel, *rk = scratch + 2 * panel, *rkp = scratch + 3 * panel;
+    const int run = update_run(nfreq, (int)t);
     hipLaunchKernelGGL(k_gj_first, dim3(t, nfreq), dim3(256), 0, s, ng, std::min(kGjNb, ng), a, pb);
     for (int c0 = 0; c0 < ng; c0 += kGjNb) {
         const int nb = std::min(kGjNb, ng - c0);
         // rows per thread x columns x threads: R W double2 values in registers
         // without spilling; measured against the neighbouring choices at 300,
         // 777, 1500, 2048, 3000 and 6000 (e.g. 6000: <6, 3, 1024> 203 ms,
-        // <12, 3, 512> 204, <6, 2, 1024> 205; 1500: <3, 16, 512> 21.5 ms)
+        // <12, 3, 512> 204, <6, 2, 1024> 205; 1500: <3, 16, 512> 21.5 ms, taken
+        // 20.9: whole calls, with the update at 1.56 and 0.54 ms a panel)
         if (ng <= 256) panel_steps<1, 16, 256>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
         else if (ng <= 512) panel_steps<1, 16, 512>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
         else if (ng <= 1024) panel_steps<2, 8, 512>(s, nfreq, ng, c0, nb, pb, rkp, piv, flag);
@@ -597,7 +645,8 @@ void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratc
         if (ng > nb)
             hipLaunchKernelGGL(k_gj_rows, dim3((unsigned)((ng + 31) / 32), nfreq), dim3(256), 0, s, ng, c0, nb, a, piv,
                                rk);
-        hipLaunchKernelGGL(k_gj_update, dim3(t, t, nfreq), dim3(256), 0, s, ng, c0, nb, a, pb, pbn, rk);
+        hipLaunchKernelGGL(k_gj_update, dim3(t, (t + run - 1) / run, nfreq), dim3(256), 0, s, ng, c0, nb, run, a, pb,
+                           pbn, rk);
         std::swap(pb, pbn);
     }
     const long rows = (long)nfreq * ng;

@@ -42,7 +42,9 @@ def _gvectors(n):
 @pytest.mark.parametrize("ng, nfreq", [
     (1, 3), (2, 1), (15, 2), (16, 1), (17, 2), (63, 1), (64, 2), (65, 1), (81, 2), (128, 1), (130, 3), (256, 1),
     (257, 2), (512, 1), (513, 1), (1024, 1), (1025, 2), (1536, 1), (1537, 1), (2048, 1), (2049, 1), (3072, 1),
-    (3073, 1), (4096, 1), (4097, 1), (6143, 1)])
+    (3073, 1), (4096, 1), (4097, 1), (6143, 1),
+    # 2, 3 and 4 row tiles per workgroup of the update, the last run short
+    (777, 5), (517, 16), (460, 28)])
 def test_inverse_with_distant_pivots(ctx, rp, ng, nfreq):
     print(f"[invert] ng={ng} nfreq={nfreq}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(ng)
