@@ -18,7 +18,7 @@
 // compiled with the accumulators in ordinary registers.  (A 64 x 64 tile for
 // four frequencies on one wave per SIMD kept its 256 accumulators in AGPRs
 // and moved all of them to and fro once per chunk: 48.8 TFLOP/s on 16 000
-// pairs at N_G = 1500 and 20 frequencies, now 65.0; 59.6 of the Hermitian half.)
+// pairs at N_G = 1500 and 20 frequencies, now 65.0; 58.8 of the Hermitian half.)
 //
 // The pair dimension is consumed in chunks of 16 pairs staged through LDS with
 // two buffers: while the matrix cores work on one chunk, the next chunk's rows

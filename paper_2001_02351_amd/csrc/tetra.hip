@@ -374,6 +374,8 @@ constexpr int kWFreqs = 2 * kWLanes;              // frequencies per pass over t
 constexpr int kWMinFreqs = 2;                     // fewest frequencies per workgroup
 constexpr int kMoments = 72;                      // 0.6^72 = 1.1e-16
 constexpr double kSeriesRatio = 0.6;
+constexpr int kCutPairs = 2;                      // pairs whose tetrahedra are cut at a time (one wave each)
+static_assert(2 * kWFreqs <= 32, "a pass's frequencies, z and z', in the bits of a word");
 static_assert(kWLanes == 8 && kWTets == 3, "eight threads per pair, three tetrahedra each");
 
 template <int CTRL> __device__ __forceinline__ double dpp(double v)
@@ -413,7 +415,7 @@ __device__ __forceinline__ double sum8(double v)
 // (pair, frequency) evaluating all 24 tetrahedra, 46% of the lanes active, the
 // weights of 128 000 pairs x 20 real frequencies (48^3 workload) took 6.39 ms,
 // now 1.70; 16 imaginary frequencies 1.33 ms, now 0.19; a metal's 14 112 pairs
-// x 10 frequencies 7.45 ms, now 0.99; 3 072 pairs x 10 0.76 ms, now 0.20.
+// x 10 frequencies 7.45 ms, now 0.86; 3 072 pairs x 10 0.76 ms, now 0.20.
 //
 // METAL: the Fermi level ef (hartree) cuts the tetrahedra.  With E_b < ef at
 // all four corners of a tetrahedron and E_a > ef at all four, the insulating
@@ -434,13 +436,13 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
     __shared__ double sC[kWPairs], sR[kWPairs], sFac[kWPairs];
     __shared__ double2 sL[kWPairs][15];
     __shared__ double2 sVal[kWPairs * 24];
-    // entries (frequency, pair, which of z and z'): from the front those of uncut
-    // tetrahedra, from the back (METAL) those of pairs with cut ones
+    // entries (frequency, pair, which of z and z') of uncut tetrahedra; METAL, a
+    // pair with cut ones: bits 2 f, 2 f + 1 for z and z' of the pass's frequency f
     __shared__ int sQueue[kWPairs * kWFreqs];
-    __shared__ int sNq, sNcut, sSome[kWPairs];   // sSome: 0 nothing, 1 some, 2 whole tetrahedra only
-    __shared__ Piece sPc[METAL ? 24 * kMaxPieces : 1];
-    __shared__ int sNpc;
-    __shared__ double2 sSum[kWThreads / 64];
+    __shared__ int sNq, sSome[kWPairs];   // sSome: 0 nothing, 1 some, 2 whole tetrahedra only
+    __shared__ unsigned sCut[kWPairs];
+    __shared__ Piece sPc[METAL ? kCutPairs : 1][METAL ? 24 * kMaxPieces : 1];
+    __shared__ int sNpc[kCutPairs];
     const int tid = threadIdx.x;
     const long p0 = (long)blockIdx.x * kWPairs;
     const int fa = blockIdx.y * fper, fb = min(nfreq, fa + fper);
@@ -597,7 +599,8 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
     }
     __syncthreads();
     for (int fc = fa; fc < fb; fc += kWFreqs) {
-        if (tid == 0) sNq = sNcut = 0;
+        if (tid == 0) sNq = 0;
+        if (tid < kWPairs) sCut[tid] = 0;
         __syncthreads();
         // the series: thread (pair, frequency)
         const int pr = tid & (kWPairs - 1);
@@ -634,8 +637,8 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
                 if (conj_pair) x = make_double2(2.0 * x.x, 0.0);
             }
             if (far) {
-                const int at = !METAL || sSome[pr] == 2 ? atomicAdd(&sNq, 1) : kWPairs * kWFreqs - 1 - atomicAdd(&sNcut, 1);
-                sQueue[at] = ((f - fc) * kWPairs + pr) * 4 + far;
+                if (!METAL || sSome[pr] == 2) sQueue[atomicAdd(&sNq, 1)] = ((f - fc) * kWPairs + pr) * 4 + far;
+                else atomicOr(&sCut[pr], (unsigned)far << 2 * (f - fc));
             }
             if (p < npair) w[(long)f * npair + p] = cscale(x, sFac[pr] * (1.0 / 6.0));
         }
@@ -687,28 +690,34 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
             }
             __syncthreads();
         }
-        // METAL, pairs with cut tetrahedra: the workgroup takes one entry at a
-        // time, 24 threads cut its tetrahedra into pieces and every thread
-        // evaluates some of the pieces' vertex integrals (one entry alone is
-        // up to 864 of them)
+        // METAL, pairs with cut tetrahedra, two at a time: 24 lanes of a wave
+        // each cut a pair's tetrahedra into pieces, once for all frequencies;
+        // then a wave takes a (pair, frequency) and its lanes the pieces' vertex
+        // integrals (up to 864), the four of a piece side by side sharing its
+        // four logarithms
         if constexpr (METAL) {
-            for (int q = 0; q < sNcut; q++) {
-                const int item = sQueue[kWPairs * kWFreqs - 1 - q];
-                const int pi = (item >> 2) & (kWPairs - 1), f = fc + (item >> 2) / kWPairs;
-                const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
-                const bool conj_pair = dl == 0.0 && om.x == 0.0;
+            const int wave = tid >> 6, lane = tid & 63;
+            unsigned todo = (unsigned)__ballot(sCut[lane & (kWPairs - 1)] != 0);   // the same in every wave
+            while (todo) {
+                int pis[kCutPairs];
+#pragma unroll
+                for (int g = 0; g < kCutPairs; g++) {
+                    pis[g] = todo ? __ffs(todo) - 1 : -1;
+                    todo &= todo - 1;
+                }
                 __syncthreads();
-                if (tid < 24) {
+                const int mine = wave == 0 ? pis[0] : wave == 1 ? pis[1] : -1;
+                if (lane < 24 && mine >= 0) {
                     double e4[4], b4[4], a4[4];
                     bool all_in = true, none_b = true, none_a = true;
                     int iv = 0, n = 0;
                     Piece pc[kMaxPieces];
 #pragma unroll
                     for (int v = 0; v < 4; v++) {
-                        const int sl = c_tetra.slot[tid][v];
-                        e4[v] = sE[sl][pi];
-                        b4[v] = sB[sl][pi];
-                        a4[v] = sA[sl][pi];
+                        const int sl = c_tetra.slot[lane][v];
+                        e4[v] = sE[sl][mine];
+                        b4[v] = sB[sl][mine];
+                        a4[v] = sA[sl][mine];
                         if (sl == kTet.self) iv = v;
                         all_in = all_in && b4[v] < ef && a4[v] > ef;
                         none_b = none_b && !(b4[v] < ef);
@@ -729,49 +738,69 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
 #pragma unroll
                     for (int d = 1; d < 32; d <<= 1) {
                         const int o = __shfl_up(at, d);
-                        if (tid >= d) at += o;
+                        if (lane >= d) at += o;
                     }
-                    if (tid == 23) sNpc = at;
+                    if (lane == 23) sNpc[wave] = at;
                     at -= n;
-                    for (int i = 0; i < n; i++) sPc[at + i] = pc[i];
+                    for (int i = 0; i < n; i++) sPc[wave][at + i] = pc[i];
                 }
                 __syncthreads();
-                const int units = 4 * sNpc;
-                double2 x = make_double2(0.0, 0.0);
-                for (int zi = 0; zi < 2; zi++) {
-                    if (!(item >> zi & 1)) continue;
-                    const double2 zz = zi ? make_double2(-om.x, -om.y + dl) : make_double2(om.x, om.y + dl);
-                    for (int u = tid; u < units; u += kWThreads) {
-                        const Piece &pc = sPc[u >> 2];
-                        const double lam = pc.lam[u & 3];
-                        if (lam == 0.0) continue;
-                        double xs[5];
-                        double2 ls[5];
+                int turn = 0;
+                for (int g = 0; g < kCutPairs; g++) {
+                    const int pi = pis[g];
+                    if (pi < 0) break;
+                    const int units = 4 * sNpc[g];
+                    for (int fi = 0; fi < kWFreqs; fi++) {
+                        const unsigned far = sCut[pi] >> 2 * fi & 3u;
+                        if (!far || (turn++ & (kWThreads / 64 - 1)) != wave) continue;
+                        const int f = fc + fi;
+                        const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
+                        const bool conj_pair = dl == 0.0 && om.x == 0.0;
+                        // partial sums over lanes of units 64 h + lane + 256 j
+                        double2 x[4];
 #pragma unroll
-                        for (int v = 0; v < 4; v++) {
-                            xs[v] = pc.e[v];
-                            ls[v] = clog_d(make_double2(zz.x - xs[v], zz.y));
+                        for (int h = 0; h < 4; h++) x[h] = make_double2(0.0, 0.0);
+                        for (int zi = 0; zi < 2; zi++) {
+                            if (!(far >> zi & 1)) continue;
+                            const double2 zz = zi ? make_double2(-om.x, -om.y + dl) : make_double2(om.x, om.y + dl);
+                            for (int u = lane, h = 0; u < units; u += 64, h++) {
+                                const Piece &pc = sPc[g][u >> 2];
+                                const double lam = pc.lam[u & 3];
+                                double xs[5];
+                                double2 ls[5];
+                                xs[4] = pc.e[u & 3];
+                                ls[4] = clog_d(make_double2(zz.x - xs[4], zz.y));
+                                ls[0] = make_double2(dpp<0x00>(ls[4].x), dpp<0x00>(ls[4].y));
+                                ls[1] = make_double2(dpp<0x55>(ls[4].x), dpp<0x55>(ls[4].y));
+                                ls[2] = make_double2(dpp<0xAA>(ls[4].x), dpp<0xAA>(ls[4].y));
+                                ls[3] = make_double2(dpp<0xFF>(ls[4].x), dpp<0xFF>(ls[4].y));
+                                if (lam == 0.0) continue;
+#pragma unroll
+                                for (int v = 0; v < 4; v++) xs[v] = pc.e[v];
+                                sort5(xs, ls);
+                                const double2 d = dd4_sorted(zz, xs, ls);
+#pragma unroll
+                                for (int t = 0; t < 4; t++) {
+                                    if ((h & 3) != t) continue;
+                                    x[t].x += lam * d.x;
+                                    x[t].y += lam * d.y;
+                                }
+                            }
                         }
-                        xs[4] = pc.e[u & 3];
-                        ls[4] = (u & 3) == 0 ? ls[0] : (u & 3) == 1 ? ls[1] : (u & 3) == 2 ? ls[2] : ls[3];
-                        sort5(xs, ls);
-                        const double2 d = dd4_sorted(zz, xs, ls);
-                        x.x += lam * d.x;
-                        x.y += lam * d.y;
-                    }
-                }
 #pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    x.x += __shfl_xor(x.x, o);
-                    x.y += __shfl_xor(x.y, o);
-                }
-                if ((tid & 63) == 0) sSum[tid >> 6] = x;
-                __syncthreads();
-                if (tid == 0) {
-                    x = cadd(cadd(sSum[0], sSum[1]), cadd(sSum[2], sSum[3]));
-                    if (conj_pair) x = make_double2(2.0 * x.x, 0.0);
-                    double2 *o = w + (long)f * npair + p0 + pi;
-                    *o = cadd(*o, cscale(x, sFac[pi] * (1.0 / 6.0)));
+                        for (int h = 0; h < 4; h++)
+#pragma unroll
+                            for (int o = 1; o < 64; o <<= 1) {
+                                x[h].x += __shfl_xor(x[h].x, o);
+                                x[h].y += __shfl_xor(x[h].y, o);
+                            }
+                        if (lane == 0) {
+                            double2 v = cadd(cadd(x[0], x[1]), cadd(x[2], x[3]));
+                            if (conj_pair) v = make_double2(2.0 * v.x, 0.0);
+                            double2 *o = w + (long)f * npair + p0 + pi;
+                            *o = cadd(*o, cscale(v, sFac[pi] * (1.0 / 6.0)));
+                        }
+                    }
                 }
             }
         }
