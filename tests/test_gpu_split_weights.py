@@ -1,0 +1,65 @@
+"""The weights inside the two-term split contraction at complex frequencies,
+which takes them from divided differences alone: with one-hot pair densities
+(M_p(G) = 1 at G = p) the diagonal of chi is the weights.
+
+Tolerance: a weight is rounded to FP32 and split into two BF16 terms of 8 bits
+each, 2^-17 of each part, products with one are exact; 2^-16 |w_p|, and 1e-11
+of the largest weight for the weights themselves.
+"""
+
+import numpy as np
+import pytest
+
+import oracle
+from oracle import metal
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def rp():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2001_02351_amd as rp
+    rp.load()
+    return rp
+
+
+@pytest.fixture(scope="module")
+def ctx(rp):
+    c = rp.Context(0)
+    yield c
+    c.close()
+
+
+# pair-frequency counts below, at and past one workgroup of 128 and several
+@pytest.mark.parametrize("cut", [False, True])
+@pytest.mark.parametrize("nocc, nemp, k1, nfreq", [(1, 1, 1, 1), (2, 2, 8, 4), (3, 3, 12, 3), (1, 43, 1, 3)])
+def test_split_weights_on_the_diagonal(ctx, rp, cut, nocc, nemp, k1, nfreq):
+    print(f"[split weights] cut={cut} pairs={nocc * nemp * k1} nfreq={nfreq}", flush=True)
+    kmesh, iq = (3, 2, 2), (1, 0, 1)
+    rng = np.random.default_rng([nocc, nemp, nfreq])
+    centre = np.concatenate([np.sort(rng.uniform(-8, -4, nocc)), np.sort(rng.uniform(4, 16, nemp))])
+    E = centre + (6.0 if cut else 2.0) * rng.uniform(-1, 1, (12, nocc + nemp))
+    freq = np.linspace(0.0, 24.0, nfreq) + 0j
+    o, e = (0, nocc), (nocc, nocc + nemp)
+    mode = rp.RP_W_TETRA_METAL if cut else rp.RP_W_TETRA
+    if cut:
+        rp.rp_set_fermi_level(ctx, 0.0)
+        want = metal.weights_metal(kmesh, iq, E, None, *o, *e, 0, k1, freq, 0.1, 0.0)
+    else:
+        want = oracle.weights(kmesh, iq, E, None, *o, *e, 0, k1, freq, 0.1, 0)
+    P = nocc * nemp * k1
+    M = torch.view_as_real(torch.eye(P, dtype=torch.complex128, device="cuda")).contiguous()
+    chi = torch.empty((nfreq, P, P, 2), dtype=torch.float64, device="cuda")
+    rp.rp_chi0_accumulate(ctx, rp.make_cell(np.eye(3) * 7.0, (8, 8, 8), kmesh), iq, nocc + nemp,
+                          torch.from_numpy(np.ascontiguousarray(E)).cuda(), None, *o, *e, 0, k1, P, M, nfreq, freq, 0.1,
+                          mode, rp.RP_SPLIT_BF16, 0, chi)
+    rp.rp_synchronize(ctx)
+    got = torch.view_as_complex(chi).cpu().numpy()
+    for f in range(nfreq):
+        d = np.abs(np.diagonal(got[f]) - want[f])
+        assert (d <= 2.0 ** -16 * np.abs(want[f]) + 1e-11 * np.abs(want).max()).all()
+        assert not np.any(got[f] - np.diag(np.diagonal(got[f])))
