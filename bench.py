@@ -105,8 +105,8 @@ def recorded_traffic():
 
 
 def recorded_pair_counters():
-    """HBM bytes of the pair kernel (per launch = per k-point) and of the u-grid
-    kernels (per k-point), or None when the sources changed."""
+    """HBM bytes of the pair kernel and of the u-grid kernels, both per k-point
+    (their launches take groups of k-points), or None when the sources changed."""
     vals = _recorded(PAIR_FILE, ("pair_bytes_per_launch", "ugrid_bytes_per_k", "pair_source_sha256",
                                  "fft_source_sha256"))
     csrc = os.path.join(ROOT, "paper_2001_02351_amd", "csrc")
@@ -767,7 +767,9 @@ def qterm_leg(rp, path, ctx, d, eps_inv, reps: int = 3, cpu: bool = False):
     rp.rp_synchronize(ctx)
     t = (time.perf_counter() - t0) / reps
     nv = len(R) * nw * nw
-    flops = 8.0 * d.ng ** 2 * (nv + nw) * d.nfreq
+    # R and -R are both in the list and J(R, i, j) = J(-R, j, i): half of the
+    # exchange forms (and R = 0, i = j) are independent
+    flops = 8.0 * d.ng ** 2 * ((nv + nw) // 2 + nw) * d.nfreq
     log(f"interaction q-term: {t * 1e3:.1f} ms per q-point ({nv} exchange densities)")
     U = torch.view_as_complex(out["U"])
     V = torch.view_as_complex(out["V"])
@@ -917,7 +919,7 @@ def main():
     pc = recorded_pair_counters()
     hbm = None
     if pc is not None:
-        t_pair = split["stage_ms_per_step"]["pair"] / d.nk / 1e3      # s per k-point (one launch)
+        t_pair = split["stage_ms_per_step"]["pair"] / d.nk / 1e3      # s per k-point
         t_ugrid = split["stage_ms_per_step"]["ugrid"] / d.nk / 1e3
         alg = (prob.nocc + prob.nemp) * int(np.prod(pair_grid)) * 8 + prob.nocc * prob.nemp * d.ng * 16
         hbm = {

@@ -210,7 +210,8 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
  * rp_chi0_accumulate; its workspace (frequencies, weights, split operands,
  * partial tiles) is carved from a fixed device array of 128 MiB that the
  * library holds on each GPU it runs on until the process ends, instead of
- * the context's growable buffers, and nothing is allocated or freed.  A call
+ * the context's growable buffers, and nothing is allocated or freed (an FP64
+ * call cuts its pairs into as many partial sums as then fit).  A call
  * whose workspace would exceed 128 MiB fails with RP_E_SHAPE before anything
  * is enqueued (fewer pairs per call fit: e.g. 12 288 pairs at N_G = 89 and
  * 10 frequencies take about 98 MiB in the split form).  Every call on one GPU
@@ -388,8 +389,10 @@ rp_status rp_wannier_W(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nw
  * U, J (dev) c128[nfreq][nR][nwan][nwan]; V, X (dev) c128[nR][nwan][nwan];
  *   each may be NULL (not computed), not all four.  accumulate = 1 adds the
  *   term to what they hold.
- * Device workspace: about (nwan + C)(N_r + ng + ntail) + nfreq ng nwan complex
- * values, C <= 512 exchange densities at a time (fewer on large grids).
+ * Device workspace, complex values: about C (ng + ntail) + nfreq C ng/64 for C
+ * <= 1280 exchange densities at a time, plus 256 (ng + ntail) on grids whose
+ * edges the density kernel takes, else max(C, nwan) N_r with C <= 512 (fewer
+ * on large grids).
  * Errors: RP_E_NULL, RP_E_SHAPE, RP_E_RANGE, RP_E_UNSUPPORTED (nwan > 32,
  * nR > 4096, an FFT length), RP_E_NOMEM, RP_E_DEVICE.
  */
