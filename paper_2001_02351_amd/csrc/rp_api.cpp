@@ -537,7 +537,7 @@ static rp_status chi_enqueue(rp_ctx *ctx, const ChiJob &c, int k0, int k1, const
         {
             StageTimer t(ctx, RP_STAGE_WEIGHTS);
             launch_weights(ctx->stream, c.g.kmesh, c.g.iq, c.nband, c.E, c.T, c.o0, c.o1, c.e0, c.e1, k0, k1,
-                           c.nfreq, dfreq, c.delta, (int)c.wm, c.ef, bufs.w, c.prec == RP_SPLIT_BF16 && !c.herm);
+                           c.nfreq, dfreq, c.delta, (int)c.wm, c.ef, bufs.w, c.prec != RP_FP64 && !c.herm);
         }
         if ((st = check_launch(ctx, "weights")) != RP_OK) return st;
     }

@@ -1,14 +1,15 @@
 // Step a5 with every divided difference evaluated by itself: the weights of the
-// two-term split contraction at complex frequencies.
+// split contractions at complex frequencies.
 //
-// That contraction rounds the weights to FP32 and keeps 2^-17 of a weighted
-// operand, so a weight that differs in its 14th digit now and then changes a
-// last bit there and moves elements of chi by up to 5e-8 of their size.  The
+// These contractions round the weights to FP32, and the two-term form keeps
+// 2^-17 of a weighted operand, so a weight that differs in its 14th digit now
+// and then changes a last bit there and moves elements of chi by up to 5e-8 of
+// their size (the three-term form: 4e-8, where few pairs make up chi).  The
 // moment series of tetra.hip is the more accurate (1e-16 against up to 1e-13
 // here) and 3.7 times as fast (1.70 against 6.39 ms for 128 000 pairs x 20
 // frequencies), but its weights change about ten such roundings of 5 million;
 // with these kernels chi stays the same in every bit.  Real weights (imaginary
-// axis), the three-term split and FP64 take the series.
+// axis) and FP64 take the series.
 #include "tetra_dd.h"
 
 namespace rp {

@@ -1,5 +1,5 @@
-"""The weights inside the two-term split contraction at complex frequencies,
-which takes them from divided differences alone: with one-hot pair densities
+"""The weights inside the split contractions at complex frequencies, which take
+them from divided differences alone: with one-hot pair densities
 (M_p(G) = 1 at G = p) the diagonal of chi is the weights.
 
 Tolerance: a weight is rounded to FP32 and split into two BF16 terms of 8 bits
@@ -35,9 +35,10 @@ def ctx(rp):
 
 
 # pair-frequency counts below, at and past one workgroup of 128 and several
+@pytest.mark.parametrize("prec", ["RP_SPLIT_BF16", "RP_SPLIT_BF16_X6"])
 @pytest.mark.parametrize("cut", [False, True])
 @pytest.mark.parametrize("nocc, nemp, k1, nfreq", [(1, 1, 1, 1), (2, 2, 8, 4), (3, 3, 12, 3), (1, 43, 1, 3)])
-def test_split_weights_on_the_diagonal(ctx, rp, cut, nocc, nemp, k1, nfreq):
+def test_split_weights_on_the_diagonal(ctx, rp, prec, cut, nocc, nemp, k1, nfreq):
     print(f"[split weights] cut={cut} pairs={nocc * nemp * k1} nfreq={nfreq}", flush=True)
     kmesh, iq = (3, 2, 2), (1, 0, 1)
     rng = np.random.default_rng([nocc, nemp, nfreq])
@@ -56,7 +57,7 @@ def test_split_weights_on_the_diagonal(ctx, rp, cut, nocc, nemp, k1, nfreq):
     chi = torch.empty((nfreq, P, P, 2), dtype=torch.float64, device="cuda")
     rp.rp_chi0_accumulate(ctx, rp.make_cell(np.eye(3) * 7.0, (8, 8, 8), kmesh), iq, nocc + nemp,
                           torch.from_numpy(np.ascontiguousarray(E)).cuda(), None, *o, *e, 0, k1, P, M, nfreq, freq, 0.1,
-                          mode, rp.RP_SPLIT_BF16, 0, chi)
+                          mode, getattr(rp, prec), 0, chi)
     rp.rp_synchronize(ctx)
     got = torch.view_as_complex(chi).cpu().numpy()
     for f in range(nfreq):
