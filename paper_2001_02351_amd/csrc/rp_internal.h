@@ -191,17 +191,17 @@ int pair_lane_edge(int need, int limit, int ng, int L3, bool fp32);
 void launch_pairs(hipStream_t s, const FftPlan plans[3], const int fft[3], const void *u, int nO, int nE, int ng,
                   const int *gsph, int L3, int n, const KGroup &grp, bool fp32, double2 *M, const SplitOps &ops);
 
-// tetra.hip: weights of a pair range.
+// tetra.hip: weights of a pair range; direct: every divided difference by itself.
 void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nband,
                     const double *E_eV, const double *T, int o0, int o1, int e0, int e1,
                     int k0, int k1, int nfreq, const double2 *freq_eV, double delta_eV,
                     int mode, double ef_eV, double2 *w, bool direct = false);
 
-// weights_direct.hip: the same with every divided difference by itself (ef in
-// hartree; not for RP_W_SAMPLING).
+// weights_direct.hip: those of a metal with every divided difference by itself
+// (ef in hartree).
 void launch_weights_direct(hipStream_t s, const int kmesh[3], const int iq[3], int nband, const double *E_eV,
                            const double *T, int o0, int o1, int e0, int e1, int k0, int k1, int nfreq,
-                           const double2 *freq_eV, double delta_eV, bool metal, double ef, double2 *w);
+                           const double2 *freq_eV, double delta_eV, double ef, double2 *w);
 
 // chi_f64.hip: chi += sum_p w_p M_p M_p^H on FP64 matrix cores.  herm: the
 // weights are real and only the upper tiles are formed (chi Hermitian).  Few

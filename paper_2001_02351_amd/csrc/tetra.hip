@@ -121,13 +121,18 @@ __device__ __forceinline__ double sum8(double v)
 // now 1.70; 16 imaginary frequencies 1.33 ms, now 0.19; a metal's 14 112 pairs
 // x 10 frequencies 7.45 ms, now 0.86; 3 072 pairs x 10 0.76 ms, now 0.20.
 //
+// Without SERIES (the split contractions of an insulator at complex
+// frequencies, see weights_direct.hip for the reason) every entry goes to the
+// list, with the bits of the one-thread form: 25^3 cRPA q-point 0.7 -> 0.34 ms
+// of weights, the 48^3 launch 6.39 -> 5.75.
+//
 // METAL: the Fermi level ef (hartree) cuts the tetrahedra.  With E_b < ef at
 // all four corners of a tetrahedron and E_a > ef at all four, the insulating
 // integral applies; with E_b >= ef or E_a <= ef at all four, the tetrahedron
 // contributes nothing; otherwise its part where E_b < ef < E_a is tiled by
 // smaller tetrahedra (clipped_pieces), whose moments (for all frequencies at
 // once) or integrals replace its own.
-template <bool METAL>
+template <bool METAL, bool SERIES>
 __global__ void __launch_bounds__(kWThreads, METAL ? 1 : 2)
 k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T,
           int o0, int nO, int e0, int nE, int k0, long npair, int nfreq, int fper, const double2 *freq,
@@ -136,7 +141,7 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
     __shared__ double sE[15][kWPairs];
     __shared__ double sB[METAL ? 15 : 1][kWPairs];
     __shared__ double sA[METAL ? 15 : 1][kWPairs];
-    __shared__ double sMu[kMoments][kWPairs];
+    __shared__ double sMu[SERIES ? kMoments : 1][kWPairs];
     __shared__ double sC[kWPairs], sR[kWPairs], sFac[kWPairs];
     __shared__ double2 sL[kWPairs][15];
     __shared__ double2 sVal[kWPairs * 24];
@@ -184,7 +189,7 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
     }
     __syncthreads();
     // moments: thread (slot, lane8) takes tetrahedra 3 lane8 .. 3 lane8 + 2
-    {
+    if constexpr (SERIES) {
         double lo = sE[0][slot], hi = lo;
 #pragma unroll
         for (int j = 1; j < 15; j++) {
@@ -309,7 +314,7 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
         // the series: thread (pair, frequency)
         const int pr = tid & (kWPairs - 1);
         const long p = p0 + pr;
-        const double c = sC[pr], R = sR[pr];
+        const double c = SERIES ? sC[pr] : 0.0, R = SERIES ? sR[pr] : 0.0;
         for (int f = fc + tid / kWPairs; f < min(fb, fc + kWFreqs); f += kWLanes) {
             const double2 om = make_double2(freq[f].x * ha, freq[f].y * ha);
             // on the imaginary axis without broadening z' = z*, and since the
@@ -317,7 +322,9 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
             const bool conj_pair = dl == 0.0 && om.x == 0.0;
             double2 x = make_double2(0.0, 0.0);
             int far = 0;   // bit zi: z (0) or z' (1) is left to the exact integrals
-            if (p < npair && sSome[pr]) {
+            if constexpr (!SERIES) {
+                if (p < npair) far = conj_pair ? 1 : 3;
+            } else if (p < npair && sSome[pr]) {
                 for (int zi = 0; zi < (conj_pair ? 1 : 2); zi++) {
                     const double2 u = zi ? make_double2(-om.x - c, -om.y + dl) : make_double2(om.x - c, om.y + dl);
                     const double a2 = u.x * u.x + u.y * u.y;
@@ -344,7 +351,7 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
                 if (!METAL || sSome[pr] == 2) sQueue[atomicAdd(&sNq, 1)] = ((f - fc) * kWPairs + pr) * 4 + far;
                 else atomicOr(&sCut[pr], (unsigned)far << 2 * (f - fc));
             }
-            if (p < npair) w[(long)f * npair + p] = cscale(x, sFac[pr] * (1.0 / 6.0));
+            if (SERIES && p < npair) w[(long)f * npair + p] = cscale(x, sFac[pr] * (1.0 / 6.0));
         }
         __syncthreads();
         // the rest, 32 entries at a time: one thread per (entry, tetrahedron),
@@ -390,7 +397,8 @@ k_weights(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const doubl
                 const int pi = (own >> 2) & (kWPairs - 1), f = fc + (own >> 2) / kWPairs;
                 if (dl == 0.0 && freq[f].x == 0.0) x = make_double2(2.0 * x.x, 0.0);   // z' = z*
                 double2 *o = w + (long)f * npair + p0 + pi;
-                *o = cadd(*o, cscale(x, sFac[pi] * (1.0 / 6.0)));
+                if (SERIES) *o = cadd(*o, cscale(x, sFac[pi] * (1.0 / 6.0)));
+                else *o = cscale(cscale(x, 1.0 / 6.0), sFac[pi]);
             }
             __syncthreads();
         }
@@ -677,9 +685,9 @@ void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nban
         return;
     }
     // the split forms at complex frequencies: the same bits as ever (weights_direct.hip)
-    if (direct) {
+    if (direct && mode == RP_W_TETRA_METAL) {
         launch_weights_direct(s, kmesh, iq, nband, E_eV, T, o0, o1, e0, e1, k0, k1, nfreq, freq_eV, delta_eV,
-                              mode == RP_W_TETRA_METAL, ef_eV / kHartreeEv, w);
+                              ef_eV / kHartreeEv, w);
         return;
     }
     // frequencies per workgroup: all of them where the pairs alone give two
@@ -694,8 +702,9 @@ void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nban
                            E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, fper, freq_eV, delta_eV,
                            ef_eV / kHartreeEv, w);
     };
-    if (mode == RP_W_TETRA_METAL) go(k_weights<true>);
-    else go(k_weights<false>);
+    if (mode == RP_W_TETRA_METAL) go(k_weights<true, true>);
+    else if (direct) go(k_weights<false, false>);
+    else go(k_weights<false, true>);
 }
 
 void launch_fermi_plasma(hipStream_t s, const int kmesh[3], int nband, const double *E_eV, const double *T, int b0,

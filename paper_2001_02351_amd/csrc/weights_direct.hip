@@ -1,15 +1,17 @@
-// Step a5 with every divided difference evaluated by itself: the weights of the
-// split contractions at complex frequencies.
+// Step a5 for a metal with every divided difference evaluated by itself: the
+// weights of the split contractions at complex frequencies.
 //
 // These contractions round the weights to FP32, and the two-term form keeps
 // 2^-17 of a weighted operand, so a weight that differs in its 14th digit now
 // and then changes a last bit there and moves elements of chi by up to 5e-8 of
 // their size (the three-term form: 4e-8, where few pairs make up chi).  The
 // moment series of tetra.hip is the more accurate (1e-16 against up to 1e-13
-// here) and 3.7 times as fast (1.70 against 6.39 ms for 128 000 pairs x 20
-// frequencies), but its weights change about ten such roundings of 5 million;
-// with these kernels chi stays the same in every bit.  Real weights (imaginary
-// axis) and FP64 take the series.
+// here) and the faster (14 112 pairs x 10 frequencies: 0.86 against 7.45 ms),
+// but its weights change about ten such roundings of 5 million; with this
+// kernel chi stays the same in every bit.  Insulators have k_weights without
+// its series for this, which has the same bits; a cut tetrahedron's pieces are
+// summed there in another order.  Real weights (imaginary axis) and FP64 take
+// the series.
 #include "tetra_dd.h"
 
 namespace rp {
@@ -75,21 +77,20 @@ constexpr int kDThreads = 128;
 // (four corners, k's corner doubled) together with their logarithms and
 // evaluates I_v(z) and I_v(z') (only I_v(z) when z' = z*).
 //
-// METAL: the Fermi level ef (hartree) cuts the tetrahedra.  With E_b < ef at
+// The Fermi level ef (hartree) cuts the tetrahedra.  With E_b < ef at
 // all four corners of a tetrahedron and E_a > ef at all four, the insulating
 // integral applies; with E_b >= ef or E_a <= ef at all four, the tetrahedron
 // contributes nothing; otherwise clipped_vertex_integral tiles the part where
 // E_b < ef < E_a (the corner energies of both bands are kept in LDS too).
-template <bool METAL>
 __global__ void __launch_bounds__(kDThreads)
-k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T,
-          int o0, int nO, int e0, int nE, int k0, long npair, int nfreq, const double2 *freq,
-          double delta, double ef, double2 *w)
+k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T, int o0,
+                 int nO, int e0, int nE, int k0, long npair, int nfreq, const double2 *freq, double delta, double ef,
+                 double2 *w)
 {
     double eR[15];
     __shared__ double2 sL[15][kDThreads];
-    __shared__ double sB[METAL ? 15 : 1][kDThreads];
-    __shared__ double sA[METAL ? 15 : 1][kDThreads];
+    __shared__ double sB[15][kDThreads];
+    __shared__ double sA[15][kDThreads];
     const int tid = threadIdx.x;
     const long t = (long)blockIdx.x * blockDim.x + tid;
     if (t >= npair * nfreq) return;
@@ -113,10 +114,8 @@ k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, cons
         const int kvq = (mesh_wrap(m1 + q1, K1) * K2 + mesh_wrap(m2 + q2, K2)) * K3 + mesh_wrap(m3 + q3, K3);
         const double eb = E[(long)kv * nband + b] * ha, ea = E[(long)kvq * nband + a] * ha;
         eR[j] = (E[(long)kvq * nband + a] - E[(long)kv * nband + b]) * ha;
-        if constexpr (METAL) {
-            sB[j][tid] = eb;
-            sA[j][tid] = ea;
-        }
+        sB[j][tid] = eb;
+        sA[j][tid] = ea;
     }
     // on the imaginary axis without broadening z' = z*, and since the
     // corner energies are real I_v(z*) = conj(I_v(z)): x = 2 Re sum I_v(z)/6
@@ -127,26 +126,24 @@ k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, cons
 #pragma unroll
         for (int j = 0; j < 15; j++) sL[j][tid] = clog_d(make_double2(zz.x - eR[j], zz.y));
         for (int tt = 0; tt < 24; tt++) {
-            if constexpr (METAL) {
-                double e4[4], b4[4], a4[4];
-                bool all_in = true, none_b = true, none_a = true;
-                int iv = 0;
+            double e4[4], b4[4], a4[4];
+            bool all_in = true, none_b = true, none_a = true;
+            int iv = 0;
 #pragma unroll
-                for (int v = 0; v < 4; v++) {
-                    const int sl = c_tetra.slot[tt][v];
-                    e4[v] = eR[sl];
-                    b4[v] = sB[sl][tid];
-                    a4[v] = sA[sl][tid];
-                    if (sl == kTet.self) iv = v;
-                    all_in = all_in && b4[v] < ef && a4[v] > ef;
-                    none_b = none_b && !(b4[v] < ef);
-                    none_a = none_a && !(a4[v] > ef);
-                }
-                if (none_b || none_a) continue;
-                if (!all_in) {
-                    x = cadd(x, clipped_vertex_integral(zz, e4, b4, a4, ef, iv));
-                    continue;
-                }
+            for (int v = 0; v < 4; v++) {
+                const int sl = c_tetra.slot[tt][v];
+                e4[v] = eR[sl];
+                b4[v] = sB[sl][tid];
+                a4[v] = sA[sl][tid];
+                if (sl == kTet.self) iv = v;
+                all_in = all_in && b4[v] < ef && a4[v] > ef;
+                none_b = none_b && !(b4[v] < ef);
+                none_a = none_a && !(a4[v] > ef);
+            }
+            if (none_b || none_a) continue;
+            if (!all_in) {
+                x = cadd(x, clipped_vertex_integral(zz, e4, b4, a4, ef, iv));
+                continue;
             }
             double xs[5];
             double2 ls[5];
@@ -173,16 +170,12 @@ k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, cons
 
 void launch_weights_direct(hipStream_t s, const int kmesh[3], const int iq[3], int nband, const double *E_eV,
                            const double *T, int o0, int o1, int e0, int e1, int k0, int k1, int nfreq,
-                           const double2 *freq_eV, double delta_eV, bool metal, double ef, double2 *w)
+                           const double2 *freq_eV, double delta_eV, double ef, double2 *w)
 {
     const long npair = (long)(k1 - k0) * (e1 - e0) * (o1 - o0);
     const dim3 grid((unsigned)((npair * nfreq + kDThreads - 1) / kDThreads));
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(kDThreads), 0, s, kmesh[0], kmesh[1], kmesh[2], iq[0], iq[1], iq[2], nband,
-                           E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, freq_eV, delta_eV, ef, w);
-    };
-    if (metal) go(k_weights_direct<true>);
-    else go(k_weights_direct<false>);
+    hipLaunchKernelGGL(k_weights_direct, grid, dim3(kDThreads), 0, s, kmesh[0], kmesh[1], kmesh[2], iq[0], iq[1], iq[2],
+                       nband, E_eV, T, o0, o1 - o0, e0, e1 - e0, k0, npair, nfreq, freq_eV, delta_eV, ef, w);
 }
 
 }  // namespace rp
