@@ -210,11 +210,13 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
  * rp_chi0_accumulate; its workspace (frequencies, weights, split operands,
  * partial tiles) is carved from a fixed device array of 128 MiB that the
  * library holds on each GPU it runs on until the process ends, instead of
- * the context's growable buffers, and nothing is allocated or freed (an FP64
- * call cuts its pairs into as many partial sums as then fit).  A call
+ * the context's growable buffers, and nothing is allocated or freed; chi is
+ * the same, bit for bit (partial sums of an FP64 call that the array cannot
+ * hold for all frequencies at once are formed for fewer at a time).  A call
  * whose workspace would exceed 128 MiB fails with RP_E_SHAPE before anything
  * is enqueued (fewer pairs per call fit: e.g. 12 288 pairs at N_G = 89 and
- * 10 frequencies take about 98 MiB in the split form).  Every call on one GPU
+ * 10 frequencies take about 98 MiB in the split form; an FP64 call needs only
+ * its frequencies and weights there).  Every call on one GPU
  * shares that array: calls that overlap on one GPU (contexts on different
  * streams) race and must be ordered by the caller; each call writes every
  * workspace byte it reads.

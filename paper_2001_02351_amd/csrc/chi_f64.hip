@@ -252,10 +252,17 @@ unsigned f64_tiles(int ng, int cb, bool herm)
 // tiles x frequency pairs take ceil(u s / 512) rounds of nchunk / s chunks,
 // plus about six chunks' time per round to fill and store, plus the partial
 // tiles written and read (about 0.0075 chunk times each).  The s of least cost
-// is taken, with at least eight chunks per slice and the partial chi within
-// part_max bytes.
-F64Shape f64_shape(long npair, int ng, int nfreq, bool herm, size_t part_max)
+// is taken, with at least eight chunks per slice.  It depends on the sizes alone,
+// never on the room an entry point has, so that all of them sum alike: the
+// partial chi of all frequencies is at most kF64PartMax (16 slices of 20
+// frequencies at N_G = 200 are 205 MB), that of one frequency at most what the
+// frequencies and weights leave of the fixed workspace where they fit in it.
+constexpr size_t kF64PartMax = (size_t)256 << 20;
+
+F64Shape f64_shape(long npair, int ng, int nfreq, bool herm)
 {
+    const size_t fixed = align256(sizeof(double2) * nfreq) + align256(sizeof(double2) * (size_t)std::max(1L, npair) * nfreq);
+    const size_t one_max = fixed <= kScratchBytes ? kScratchBytes - fixed : kF64PartMax;
     F64Shape best;
     constexpr double rate[] = {62.0, 64.0, 66.0, 67.0};
     double least = 1e300;
@@ -271,7 +278,8 @@ F64Shape f64_shape(long npair, int ng, int nfreq, bool herm, size_t part_max)
     const long nchunk = (npair + kKC - 1) / kKC;
     double cost = 1e300;
     for (int s = 1; s <= 64 && (s == 1 || nchunk / s >= 8); s++) {
-        if (s > 1 && sizeof(double2) * (size_t)s * nfreq * ng * ng > part_max) break;
+        const size_t one = sizeof(double2) * (size_t)s * ng * ng;
+        if (s > 1 && (one * nfreq > kF64PartMax || one > one_max)) break;
         const double c = std::ceil(u * s / 512.0) * ((double)nchunk / s + 6.0) + (s > 1 ? 0.0075 * u * s : 0.0);
         if (c < cost) {
             cost = c;
@@ -283,29 +291,38 @@ F64Shape f64_shape(long npair, int ng, int nfreq, bool herm, size_t part_max)
 
 }  // namespace
 
-size_t chi_f64_part_bytes(long npair, int ng, int nfreq, bool herm, size_t part_max)
+size_t chi_f64_part_bytes(long npair, int ng, int nfreq, bool herm)
 {
-    const F64Shape sh = f64_shape(npair, ng, nfreq, herm, part_max);
+    const F64Shape sh = f64_shape(npair, ng, nfreq, herm);
     return sh.nslice > 1 ? sizeof(double2) * (size_t)sh.nslice * nfreq * ng * ng : 0;
 }
 
 void launch_chi_f64(hipStream_t s, long npair, int ng, const double2 *M, int nfreq, const double2 *w,
-                    int accumulate, bool herm, size_t part_max, void *part, double2 *chi)
+                    int accumulate, bool herm, void *part, size_t part_bytes, double2 *chi)
 {
-    const F64Shape sh = f64_shape(npair, ng, nfreq, herm, part_max);
-    double2 *out = sh.nslice > 1 ? (double2 *)part : chi;
-    const dim3 grid(sh.tiles, (unsigned)sh.nslice, (unsigned)((nfreq + 1) / 2));
-    auto go = [&](auto kern) {
-        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, npair, ng, M, nfreq, w, accumulate, (int)herm, sh.nslice, out);
-    };
-    if (sh.cb == 5) go(k_chi_f64<5>);
-    else if (sh.cb == 4) go(k_chi_f64<4>);
-    else if (sh.cb == 3) go(k_chi_f64<3>);
-    else go(k_chi_f64<2>);
-    if (sh.nslice > 1) {
-        const long n = (long)nfreq * ng * ng;
-        hipLaunchKernelGGL(k_chi_f64_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ng, nfreq, sh.nslice,
-                           accumulate, (int)herm, (const double2 *)part, chi);
+    F64Shape sh = f64_shape(npair, ng, nfreq, herm);
+    // as many frequencies at a time as part holds (in twos, like the kernel's)
+    const long n2 = (long)ng * ng;
+    const size_t fit = part_bytes / (sizeof(double2) * (size_t)sh.nslice * n2);
+    if (!fit) sh.nslice = 1;
+    const int per = sh.nslice == 1 || fit >= (size_t)nfreq ? nfreq : fit > 1 ? (int)fit & ~1 : 1;
+    for (int fa = 0; fa < nfreq; fa += per) {
+        const int nf = std::min(per, nfreq - fa);
+        double2 *x = chi + fa * n2, *out = sh.nslice > 1 ? (double2 *)part : x;
+        const dim3 grid(sh.tiles, (unsigned)sh.nslice, (unsigned)((nf + 1) / 2));
+        auto go = [&](auto kern) {
+            hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, npair, ng, M, nf, w + fa * npair, accumulate, (int)herm,
+                               sh.nslice, out);
+        };
+        if (sh.cb == 5) go(k_chi_f64<5>);
+        else if (sh.cb == 4) go(k_chi_f64<4>);
+        else if (sh.cb == 3) go(k_chi_f64<3>);
+        else go(k_chi_f64<2>);
+        if (sh.nslice > 1) {
+            const long n = nf * n2;
+            hipLaunchKernelGGL(k_chi_f64_sum, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, ng, nf, sh.nslice,
+                               accumulate, (int)herm, (const double2 *)part, x);
+        }
     }
 }
 

@@ -426,10 +426,6 @@ static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, con
 
 // ---- steps a5-a6: validated weight and contraction work -------------------
 
-// Most bytes of partial chi that a sliced FP64 contraction may take (slices
-// matter where chi is small: 16 slices of 20 frequencies at N_G = 200 are 205 MB).
-constexpr size_t kF64PartMax = (size_t)256 << 20;
-
 struct ChiJob {
     Geometry g;
     int nband = 0;
@@ -443,7 +439,6 @@ struct ChiJob {
     rp_precision prec = RP_FP64;
     bool herm = false;  // real weights: chi Hermitian
     Tune tune;          // contraction launch shape
-    size_t part_max = kF64PartMax;  // bound on the FP64 contraction's partial chi
 };
 
 static rp_status weights_check(rp_ctx *ctx, const double *E, int nfreq, const double *freq_eV, double delta_eV,
@@ -506,7 +501,7 @@ static ChiBytes chi_bytes(const ChiJob &c, long npair)
     ChiBytes b;
     b.w = sizeof(double2) * (size_t)std::max(1L, npair) * c.nfreq;
     if (c.prec == RP_FP64) {
-        b.part = chi_f64_part_bytes(npair, c.ng, c.nfreq, c.herm, c.part_max);
+        b.part = chi_f64_part_bytes(npair, c.ng, c.nfreq, c.herm);
     } else {
         b.a = split_a_bytes(npair, c.ng);
         b.b = split_b_bytes(npair, c.ng);
@@ -517,9 +512,20 @@ static ChiBytes chi_bytes(const ChiJob &c, long npair)
     return b;
 }
 
+// The same for npk pairs per k-point, kbatch of nk k-points at a time: the FP64
+// slice count follows the sizes, so the short last batch may take more of them.
+static ChiBytes chi_batch_bytes(const ChiJob &c, long npk, int kbatch, int nk)
+{
+    ChiBytes b = chi_bytes(c, npk * std::min(kbatch, std::max(1, nk)));
+    if (c.prec == RP_FP64 && nk > kbatch && nk % kbatch)
+        b.part = std::max(b.part, chi_bytes(c, npk * (nk % kbatch)).part);
+    return b;
+}
+
 struct ChiBufs {
     double2 *w;
     void *a, *b, *sw, *part;
+    size_t part_bytes;
 };
 
 // Enqueues the weights of the pairs of k in [k0, k1) into bufs.w (dfreq is the
@@ -543,7 +549,7 @@ static rp_status chi_enqueue(rp_ctx *ctx, const ChiJob &c, int k0, int k1, const
     }
     if (c.prec == RP_FP64) {
         StageTimer t(ctx, RP_STAGE_CHI);
-        launch_chi_f64(ctx->stream, npair, c.ng, M, c.nfreq, bufs.w, accumulate, c.herm, c.part_max, bufs.part, chi);
+        launch_chi_f64(ctx->stream, npair, c.ng, M, c.nfreq, bufs.w, accumulate, c.herm, bufs.part, bufs.part_bytes, chi);
     } else {
         const int nterm = c.prec == RP_SPLIT_BF16 ? 2 : 3;
         {
@@ -576,7 +582,6 @@ template <typename T> static void key_val(std::string &key, const T &v) { key_pu
 // kScratchBytes until the process ends.  Host code never uses the name
 // `scratch` as an address: the device address comes from hipGetSymbolAddress,
 // once per device with that device current, and is kept per device.
-constexpr size_t kScratchBytes = (size_t)128 << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 static std::mutex g_scratch_mu;
@@ -801,7 +806,7 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
     if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, freq_eV, sizeof(double2) * nfreq)) != RP_OK) return st;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
-                       ctx->chi_part.p};
+                       ctx->chi_part.p, ctx->chi_part.bytes};
     return chi_enqueue(ctx, c, k0, k1, (const double2 *)M, (const double2 *)ctx->freq.p, bufs, accumulate,
                        (double2 *)chi);
 }
@@ -823,14 +828,12 @@ rp_status rp_chi0_accumulate_noalloc(rp_ctx *ctx, const rp_cell *cell, const int
     // the workspace of rp_chi0_accumulate, carved from the fixed array in
     // 256-byte aligned pieces: frequencies, weights, split operands, partial tiles
     const long npair = (long)(k1 - k0) * (e1 - e0) * (o1 - o0);
-    auto up = [](size_t n) { return (n + 255) / 256 * 256; };
-    // an FP64 contraction cuts fewer slices where the rest of the array is small
-    const size_t fixed = up(sizeof(double2) * nfreq) + up(sizeof(double2) * (size_t)std::max(1L, npair) * nfreq);
-    c.part_max = std::min(kF64PartMax, fixed < kScratchBytes ? kScratchBytes - fixed : 0);
     const ChiBytes nb = chi_bytes(c, npair);
-    const size_t off_f = 0, off_w = up(sizeof(double2) * nfreq);
-    const size_t off_a = off_w + up(nb.w), off_b = off_a + up(nb.a), off_sw = off_b + up(nb.b);
-    const size_t off_part = off_sw + up(nb.sw), need = off_part + up(nb.part);
+    const size_t off_f = 0, off_w = align256(sizeof(double2) * nfreq);
+    const size_t off_a = off_w + align256(nb.w), off_b = off_a + align256(nb.a), off_sw = off_b + align256(nb.b);
+    const size_t off_part = off_sw + align256(nb.sw);
+    // the FP64 contraction makes do with what is left for its partial chi
+    const size_t need = off_part + (prec == RP_FP64 ? 0 : align256(nb.part));
     if (need > kScratchBytes)
         return fail(ctx, RP_E_SHAPE,
                     "this call needs %zu bytes of workspace, more than the fixed %zu (fewer pairs per call)", need,
@@ -841,7 +844,8 @@ rp_status rp_chi0_accumulate_noalloc(rp_ctx *ctx, const rp_cell *cell, const int
         (void)hipGetLastError();
         return fail(ctx, RP_E_DEVICE, "host-to-device copy of the frequencies failed");
     }
-    const ChiBufs bufs{(double2 *)(base + off_w), base + off_a, base + off_b, base + off_sw, base + off_part};
+    const ChiBufs bufs{(double2 *)(base + off_w), base + off_a, base + off_b, base + off_sw, base + off_part,
+                       kScratchBytes - off_part};
     return chi_enqueue(ctx, c, k0, k1, (const double2 *)M, (const double2 *)(base + off_f), bufs, accumulate,
                        (double2 *)chi);
 }
@@ -902,7 +906,7 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
     if (!p->chi) return fail(ctx, RP_E_NULL, "chi is NULL");
     const long npk = (long)(p->o1 - p->o0) * (p->e1 - p->e0);
     const long npair = npk * std::min(p->kbatch, std::max(1, p->k1 - p->k0));
-    const ChiBytes nb = chi_bytes(cj, pj.empty ? 0 : npair);
+    const ChiBytes nb = chi_batch_bytes(cj, pj.empty ? 0 : npk, p->kbatch, p->k1 - p->k0);
     DevBuf &grid = pj.fp32 ? ctx->ugrid32 : ctx->ugrid;
     if (!pj.empty) {
         if ((st = ensure(ctx, grid, pair_grid_bytes(pj, std::min(p->kbatch, p->k1 - p->k0)))) != RP_OK) return st;
@@ -921,7 +925,7 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
     const int *dg = (const int *)ctx->glist.p;
     const double2 *df = (const double2 *)ctx->freq.p;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
-                       ctx->chi_part.p};
+                       ctx->chi_part.p, ctx->chi_part.bytes};
     double2 *chi = (double2 *)p->chi;
     if (pj.empty) return chi_enqueue(ctx, cj, p->k0, p->k0, nullptr, df, bufs, p->accumulate, chi);
     for (int ka = p->k0; ka < p->k1; ka += p->kbatch) {
@@ -972,7 +976,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
             grid_b = std::max(grid_b, pair_grid_bytes(pj[i], std::min(p.kbatch, p.k1 - p.k0)));
             if (prec == RP_FP64) m_b = std::max(m_b, sizeof(double2) * (size_t)npair * p.ng);
         }
-        const ChiBytes b = chi_bytes(cj[i], pj[i].empty ? 0 : npair);
+        const ChiBytes b = chi_batch_bytes(cj[i], pj[i].empty ? 0 : npk, p.kbatch, p.k1 - p.k0);
         cb.w = std::max(cb.w, b.w);
         cb.a = std::max(cb.a, b.a);
         cb.b = std::max(cb.b, b.b);
@@ -1039,7 +1043,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         if ((st = upload(ctx, ctx->bstage, stage.data(), stage.size())) != RP_OK) return st;
         const char *dstage = (const char *)ctx->bstage.p;
         const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
-                           ctx->chi_part.p};
+                           ctx->chi_part.p, ctx->chi_part.bytes};
         // The launches are captured as a sequence of graphs of at most about
         // kGraphNodes kernel nodes each (a graph closes after the k batch that
         // reaches the bound), launched in order on the stream: the same launches

@@ -67,7 +67,7 @@ struct rp_ctx {
     rp::DevBuf split_a;             // split-BF16 row operand (FP32 complex)
     rp::DevBuf split_b;             // split-BF16 column operand (BF16 planes)
     rp::DevBuf split_w;             // split-BF16 weights (FP32)
-    rp::DevBuf chi_part;            // split-BF16 partial tiles of sliced pair steps
+    rp::DevBuf chi_part;            // partial chi of sliced pairs (FP64), partial tiles of sliced pair steps (split)
     rp::DevBuf rho;                 // Wannier densities
     rp::DevBuf piv;                 // pivots
     rp::DevBuf mbuf;                // pair densities of one k batch (batch entry point)
@@ -134,6 +134,11 @@ class StageTimer {
     int stage_;
     hipEvent_t a_ = nullptr;
 };
+
+// bytes of the fixed workspace of rp_chi0_accumulate_noalloc
+constexpr size_t kScratchBytes = (size_t)128 << 20;
+
+inline size_t align256(size_t n) { return (n + 255) / 256 * 256; }
 
 // ---- kernel launchers (one translation unit each) --------------------------
 
@@ -205,11 +210,13 @@ void launch_weights_direct(hipStream_t s, const int kmesh[3], const int iq[3], i
 
 // chi_f64.hip: chi += sum_p w_p M_p M_p^H on FP64 matrix cores.  herm: the
 // weights are real and only the upper tiles are formed (chi Hermitian).  Few
-// tiles are cut into slices of the pairs; part holds their partial chi,
-// chi_f64_part_bytes of it, never more than part_max (the same in both calls).
-size_t chi_f64_part_bytes(long npair, int ng, int nfreq, bool herm, size_t part_max);
+// tiles are cut into slices of the pairs; part holds their partial chi:
+// chi_f64_part_bytes for all frequencies at once.  In fewer bytes the launch
+// takes fewer frequencies at a time, with the same sums, and it is not sliced
+// where one frequency's do not fit.
+size_t chi_f64_part_bytes(long npair, int ng, int nfreq, bool herm);
 void launch_chi_f64(hipStream_t s, long npair, int ng, const double2 *M, int nfreq, const double2 *w,
-                    int accumulate, bool herm, size_t part_max, void *part, double2 *chi);
+                    int accumulate, bool herm, void *part, size_t part_bytes, double2 *chi);
 
 // chi_bf16.hip: split-BF16 contraction (herm as above; part holds the
 // partial tiles when the pair steps are sliced, chi_part_bytes of them).
