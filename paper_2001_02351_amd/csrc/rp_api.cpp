@@ -49,6 +49,18 @@ rp_status ensure(rp_ctx *ctx, DevBuf &b, size_t bytes)
     return RP_OK;
 }
 
+rp_status ensure_some(rp_ctx *ctx, DevBuf &b, size_t bytes, size_t least)
+{
+    if (bytes >= b.denied && b.bytes >= least) return RP_OK;
+    const std::string err = ctx->err;
+    for (size_t want = bytes;; want = std::max(least, want / 2)) {
+        const rp_status st = ensure(ctx, b, want);
+        if (st == RP_OK) ctx->err = err;   // a smaller size is no failure of the call
+        if (st != RP_E_NOMEM || want <= least) return st;
+        b.denied = std::min(b.denied, want);
+    }
+}
+
 rp_status check_launch(rp_ctx *ctx, const char *what)
 {
     hipError_t e = hipGetLastError();
@@ -491,9 +503,10 @@ static rp_status chi_check(rp_ctx *ctx, const rp_cell *cell, const int iq[3], in
     return RP_OK;
 }
 
-// Workspace of one contraction over npair pairs.
+// Workspace of one contraction over npair pairs.  part_least: the FP64 form
+// makes do with fewer bytes for its partial chi than all of part, or none.
 struct ChiBytes {
-    size_t w = 0, a = 0, b = 0, sw = 0, part = 0;
+    size_t w = 0, a = 0, b = 0, sw = 0, part = 0, part_least = 0;
 };
 
 static ChiBytes chi_bytes(const ChiJob &c, long npair)
@@ -508,6 +521,7 @@ static ChiBytes chi_bytes(const ChiJob &c, long npair)
         b.sw = split_w_bytes(npair, c.nfreq);
         b.part = chi_part_bytes(npair, c.ng, c.nfreq, c.herm, c.tune.chi_nw, c.tune.chi_fill, c.tune.chi_kernel,
                                 c.prec == RP_SPLIT_BF16 ? 2 : 3);
+        b.part_least = b.part;
     }
     return b;
 }
@@ -803,7 +817,7 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
     }
-    if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, freq_eV, sizeof(double2) * nfreq)) != RP_OK) return st;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
                        ctx->chi_part.p, ctx->chi_part.bytes};
@@ -919,7 +933,7 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
     }
-    if ((st = ensure(ctx, ctx->chi_part, nb.part)) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->glist, p->gsph, sizeof(int) * 3 * p->ng)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, p->freq_eV, sizeof(double2) * p->nfreq)) != RP_OK) return st;
     const int *dg = (const int *)ctx->glist.p;
@@ -982,6 +996,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         cb.b = std::max(cb.b, b.b);
         cb.sw = std::max(cb.sw, b.sw);
         cb.part = std::max(cb.part, b.part);
+        cb.part_least = std::max(cb.part_least, b.part_least);
         goff[i] = stage_b;
         stage_b += round_up(sizeof(int) * 3 * p.ng);
         foff[i] = stage_b;
@@ -998,7 +1013,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         if ((st = ensure(ctx, ctx->split_b, cb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, cb.sw)) != RP_OK) return st;
     }
-    if ((st = ensure(ctx, ctx->chi_part, cb.part)) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->chi_part, cb.part, cb.part_least)) != RP_OK) return st;
     // host staging of every G list and frequency list, one copy to the device
     std::vector<char> stage(stage_b, 0);
     for (int i = 0; i < nprob; i++) {
@@ -1030,6 +1045,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
     const void *ws[] = {grid.p,          ctx->mbuf.p,    ctx->weights.p, ctx->split_a.p,
                         ctx->split_b.p, ctx->split_w.p, ctx->chi_part.p};
     key_put(key, ws, sizeof ws);
+    key_val(key, ctx->chi_part.bytes);   // sets how many frequencies a launch takes
 
     if (ctx->batch_execs.empty() || key != ctx->batch_key) {
         if (!ctx->batch_execs.empty()) {

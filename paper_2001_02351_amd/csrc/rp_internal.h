@@ -22,6 +22,7 @@ constexpr double kHartreeEv = 27.211386245988;  // CODATA 2018
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
+    size_t denied = ~(size_t)0;   // the least size that ensure_some did not get
 };
 
 // Bits of the device-side fault flag.
@@ -109,6 +110,10 @@ namespace rp {
 
 rp_status fail(rp_ctx *ctx, rp_status st, const char *fmt, ...);
 rp_status ensure(rp_ctx *ctx, DevBuf &b, size_t bytes);
+// Workspace of which only speed needs all: `bytes` or, where the device has no
+// room for them, the largest half, quarter, .. of them that it has, `least` at
+// the least.  A size once denied is not asked for again.
+rp_status ensure_some(rp_ctx *ctx, DevBuf &b, size_t bytes, size_t least);
 rp_status check_launch(rp_ctx *ctx, const char *what);
 rp_status geometry(rp_ctx *ctx, const rp_cell *cell, const int iq[3], Geometry *g);
 
