@@ -51,7 +51,7 @@ rp_status ensure(rp_ctx *ctx, DevBuf &b, size_t bytes)
 
 rp_status ensure_some(rp_ctx *ctx, DevBuf &b, size_t bytes, size_t least)
 {
-    if (bytes >= b.denied && b.bytes >= least) return RP_OK;
+    if (bytes <= b.bytes || (bytes >= b.denied && b.bytes >= least)) return RP_OK;
     const std::string err = ctx->err;
     for (size_t want = bytes;; want = std::max(least, want / 2)) {
         const rp_status st = ensure(ctx, b, want);
@@ -369,17 +369,17 @@ static rp_status pair_check(rp_ctx *ctx, const rp_cell *cell, const int iq[3], i
 // kGroupBytes (so that the pair kernel finds them in the 256 MB last-level
 // cache: 2 of 63 MB on the 48^3 workload, u-grids 2.78 -> 2.43 ms and pairs
 // 6.64 -> 6.36 ms per 16 k-points), at least one and at most kKGroup or the
-// call's own count.
+// call's own count; fewer in a smaller workspace.
 constexpr size_t kGroupBytes = (size_t)150 << 20;
 
-static int pair_group(const PairJob &j, int nk)
+static int pair_group(const PairJob &j, int nk, size_t bytes = kGroupBytes)
 {
     const size_t one = ugrid_bytes(j.g.fft, (j.o1 - j.o0) + (j.e1 - j.e0), j.npw_max, j.fp32, 1);
-    return std::max(1, (int)std::min<size_t>({(size_t)kKGroup, (size_t)std::max(1, nk), kGroupBytes / one}));
+    return std::max(1, (int)std::min<size_t>({(size_t)kKGroup, (size_t)std::max(1, nk), kGroupBytes / one, bytes / one}));
 }
 
-// u-grid workspace of one group (of a call over nk k-points): the occupied and
-// the empty bands' grids.
+// u-grid workspace of one group (of a call over nk k-points; nk = 1: the least
+// that does): the occupied and the empty bands' grids.
 static size_t pair_grid_bytes(const PairJob &j, int nk)
 {
     return ugrid_bytes(j.g.fft, (j.o1 - j.o0) + (j.e1 - j.e0), j.npw_max, j.fp32, pair_group(j, nk));
@@ -387,11 +387,11 @@ static size_t pair_grid_bytes(const PairJob &j, int nk)
 
 // Enqueues steps a2-a4 for k in [k0, k1), a group of k-points at a time: the
 // u-grids of the occupied bands at k and of the empty bands at k+q (into
-// `grid`, of pair_grid_bytes for k1 - k0 k-points or more), then the pair
-// kernel into M[k - k0], or, when ops is given (FP32 grids), into the split
-// operands of one contraction over the pairs of [k0, k1) in M's order.  dg is
-// the device copy of the G list.  No allocation, copy or synchronization.
-static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, const int *dg, void *grid,
+// `grid`, which holds at least one k-point's), then the pair kernel into
+// M[k - k0], or, when ops is given (FP32 grids), into the split operands of one
+// contraction over the pairs of [k0, k1) in M's order.  dg is the device copy of
+// the G list.  No allocation, copy or synchronization.
+static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, const int *dg, const DevBuf &grid,
                               double2 *M, const SplitOps *ops = nullptr)
 {
     const Geometry &g = j.g;
@@ -399,7 +399,7 @@ static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, con
     if ((long)nO * nE * (k1 - k0) == 0) return RP_OK;
     const int L3 = j.hi[2] - j.lo[2] + 1;
     const BandSource src{j.miller, j.coef, j.nband, j.npw_max, j.o0, nO, j.e0, nE};
-    const int per = pair_group(j, k1 - k0);
+    const int per = pair_group(j, k1 - k0, grid.bytes);
     for (int ka = k0; ka < k1; ka += per) {
         const int n = std::min(per, k1 - ka);
         KGroup grp{};
@@ -421,13 +421,13 @@ static rp_status pair_enqueue(rp_ctx *ctx, const PairJob &j, int k0, int k1, con
         }
         {
             StageTimer t(ctx, RP_STAGE_UGRID);
-            launch_ugrids(ctx->stream, j.plans, g.fft, j.mmax, src, n, grp, grid, j.fp32, j.fft_lines);
+            launch_ugrids(ctx->stream, j.plans, g.fft, j.mmax, src, n, grp, grid.p, j.fp32, j.fft_lines);
         }
         {
             StageTimer t(ctx, RP_STAGE_PAIR);
             SplitOps o = ops ? *ops : SplitOps{};
             o.p0 = (long)(ka - k0) * nE * nO;
-            launch_pairs(ctx->stream, j.plans, g.fft, grid, nO, nE, j.ng, dg, L3, n, grp, j.fp32,
+            launch_pairs(ctx->stream, j.plans, g.fft, grid.p, nO, nE, j.ng, dg, L3, n, grp, j.fp32,
                          ops ? nullptr : M + (long)(ka - k0) * nE * nO * j.ng, o);
         }
         rp_status st = check_launch(ctx, "pair density");
@@ -754,9 +754,9 @@ rp_status rp_pair_density(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int
     if (!M) return fail(ctx, RP_E_NULL, "M is NULL");
     if (j.empty) return RP_OK;
     DevBuf &grid = j.fp32 ? ctx->ugrid32 : ctx->ugrid;
-    if ((st = ensure(ctx, grid, pair_grid_bytes(j, k1 - k0))) != RP_OK) return st;
     if ((st = upload(ctx, ctx->glist, gsph, sizeof(int) * 3 * ng)) != RP_OK) return st;
-    return pair_enqueue(ctx, j, k0, k1, (const int *)ctx->glist.p, grid.p, (double2 *)M);
+    if ((st = ensure_some(ctx, grid, pair_grid_bytes(j, k1 - k0), pair_grid_bytes(j, 1))) != RP_OK) return st;
+    return pair_enqueue(ctx, j, k0, k1, (const int *)ctx->glist.p, grid, (double2 *)M);
 }
 
 rp_status rp_pair_grid(const rp_cell *cell, const int iq[3], const int mmax[3], int ng, const int *gsph,
@@ -817,8 +817,9 @@ rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], 
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
     }
-    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
+    if ((st = ensure(ctx, ctx->chi_part, nb.part_least)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, freq_eV, sizeof(double2) * nfreq)) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
                        ctx->chi_part.p, ctx->chi_part.bytes};
     return chi_enqueue(ctx, c, k0, k1, (const double2 *)M, (const double2 *)ctx->freq.p, bufs, accumulate,
@@ -888,7 +889,7 @@ rp_status rp_set_tuning(rp_ctx *ctx, int n, const rp_tune_entry *table)
 // bufs.b directly (no FP64 M), then the contraction.  dg and df are the
 // device copies of the problem's G and frequency lists.
 static rp_status kbatch_enqueue(rp_ctx *ctx, const PairJob &pj, const ChiJob &cj, int ka, int kb, const int *dg,
-                                const double2 *df, void *grid, const ChiBufs &bufs, int accumulate, double2 *chi)
+                                const double2 *df, const DevBuf &grid, const ChiBufs &bufs, int accumulate, double2 *chi)
 {
     rp_status st;
     if (cj.prec == RP_FP64) {
@@ -922,20 +923,22 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
     const long npair = npk * std::min(p->kbatch, std::max(1, p->k1 - p->k0));
     const ChiBytes nb = chi_batch_bytes(cj, pj.empty ? 0 : npk, p->kbatch, p->k1 - p->k0);
     DevBuf &grid = pj.fp32 ? ctx->ugrid32 : ctx->ugrid;
-    if (!pj.empty) {
-        if ((st = ensure(ctx, grid, pair_grid_bytes(pj, std::min(p->kbatch, p->k1 - p->k0)))) != RP_OK) return st;
-        if (prec == RP_FP64 && (st = ensure(ctx, ctx->mbuf, sizeof(double2) * (size_t)npair * p->ng)) != RP_OK)
-            return st;
-    }
+    if (!pj.empty && prec == RP_FP64 && (st = ensure(ctx, ctx->mbuf, sizeof(double2) * (size_t)npair * p->ng)) != RP_OK)
+        return st;
     if ((st = ensure(ctx, ctx->weights, nb.w)) != RP_OK) return st;
     if (prec != RP_FP64) {
         if ((st = ensure(ctx, ctx->split_a, nb.a)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_b, nb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, nb.sw)) != RP_OK) return st;
     }
-    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
+    if ((st = ensure(ctx, ctx->chi_part, nb.part_least)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->glist, p->gsph, sizeof(int) * 3 * p->ng)) != RP_OK) return st;
     if ((st = upload(ctx, ctx->freq, p->freq_eV, sizeof(double2) * p->nfreq)) != RP_OK) return st;
+    // last what takes as much as there is
+    if (!pj.empty && (st = ensure_some(ctx, grid, pair_grid_bytes(pj, std::min(p->kbatch, p->k1 - p->k0)),
+                                       pair_grid_bytes(pj, 1))) != RP_OK)
+        return st;
+    if ((st = ensure_some(ctx, ctx->chi_part, nb.part, nb.part_least)) != RP_OK) return st;
     const int *dg = (const int *)ctx->glist.p;
     const double2 *df = (const double2 *)ctx->freq.p;
     const ChiBufs bufs{(double2 *)ctx->weights.p, ctx->split_a.p, ctx->split_b.p, ctx->split_w.p,
@@ -944,7 +947,7 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec)
     if (pj.empty) return chi_enqueue(ctx, cj, p->k0, p->k0, nullptr, df, bufs, p->accumulate, chi);
     for (int ka = p->k0; ka < p->k1; ka += p->kbatch) {
         const int kb = std::min(p->k1, ka + p->kbatch);
-        if ((st = kbatch_enqueue(ctx, pj, cj, ka, kb, dg, df, grid.p, bufs, ka == p->k0 ? p->accumulate : 1,
+        if ((st = kbatch_enqueue(ctx, pj, cj, ka, kb, dg, df, grid, bufs, ka == p->k0 ? p->accumulate : 1,
                                  chi)) != RP_OK)
             return st;
     }
@@ -968,7 +971,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
     std::vector<PairJob> pj(nprob);
     std::vector<ChiJob> cj(nprob);
     std::vector<size_t> goff(nprob), foff(nprob);
-    size_t grid_b = 0, m_b = 0, stage_b = 0;
+    size_t grid_b = 0, grid_least = 0, m_b = 0, stage_b = 0;
     ChiBytes cb;
     auto round_up = [](size_t n) { return (n + 255) / 256 * 256; };
     for (int i = 0; i < nprob; i++) {
@@ -988,6 +991,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         const long npair = npk * std::min(p.kbatch, std::max(1, p.k1 - p.k0));
         if (!pj[i].empty) {
             grid_b = std::max(grid_b, pair_grid_bytes(pj[i], std::min(p.kbatch, p.k1 - p.k0)));
+            grid_least = std::max(grid_least, pair_grid_bytes(pj[i], 1));
             if (prec == RP_FP64) m_b = std::max(m_b, sizeof(double2) * (size_t)npair * p.ng);
         }
         const ChiBytes b = chi_batch_bytes(cj[i], pj[i].empty ? 0 : npk, p.kbatch, p.k1 - p.k0);
@@ -1005,7 +1009,6 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
     const bool fp32 = prec != RP_FP64;
     DevBuf &grid = fp32 ? ctx->ugrid32 : ctx->ugrid;
     rp_status st;
-    if ((st = ensure(ctx, grid, grid_b)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->mbuf, m_b)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->weights, cb.w)) != RP_OK) return st;
     if (fp32) {
@@ -1013,6 +1016,10 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
         if ((st = ensure(ctx, ctx->split_b, cb.b)) != RP_OK) return st;
         if ((st = ensure(ctx, ctx->split_w, cb.sw)) != RP_OK) return st;
     }
+    if ((st = ensure(ctx, ctx->chi_part, cb.part_least)) != RP_OK) return st;
+    if ((st = ensure(ctx, ctx->bstage, stage_b)) != RP_OK) return st;
+    // last what takes as much as there is
+    if ((st = ensure_some(ctx, grid, grid_b, grid_least)) != RP_OK) return st;
     if ((st = ensure_some(ctx, ctx->chi_part, cb.part, cb.part_least)) != RP_OK) return st;
     // host staging of every G list and frequency list, one copy to the device
     std::vector<char> stage(stage_b, 0);
@@ -1045,7 +1052,8 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
     const void *ws[] = {grid.p,          ctx->mbuf.p,    ctx->weights.p, ctx->split_a.p,
                         ctx->split_b.p, ctx->split_w.p, ctx->chi_part.p};
     key_put(key, ws, sizeof ws);
-    key_val(key, ctx->chi_part.bytes);   // sets how many frequencies a launch takes
+    key_val(key, grid.bytes);            // set how many k-points and
+    key_val(key, ctx->chi_part.bytes);   // frequencies a launch takes
 
     if (ctx->batch_execs.empty() || key != ctx->batch_key) {
         if (!ctx->batch_execs.empty()) {
@@ -1132,7 +1140,7 @@ rp_status rp_chi0_batch(rp_ctx *ctx, int nprob, const rp_problem *probs, rp_prec
                 if (piece > 0 && piece + bound(kb - ka) > kGraphNodes) {
                     if ((st = end_piece(RP_OK)) != RP_OK || (st = begin_piece()) != RP_OK) break;
                 }
-                st = kbatch_enqueue(ctx, pj[i], cj[i], ka, kb, dg, df, grid.p, bufs, ka == p.k0 ? p.accumulate : 1,
+                st = kbatch_enqueue(ctx, pj[i], cj[i], ka, kb, dg, df, grid, bufs, ka == p.k0 ? p.accumulate : 1,
                                     chi);
                 piece += bound(kb - ka);
             }

@@ -138,11 +138,11 @@ def bands(nk, npw): return np.full(nk, npw, np.int32)
 def pair(kmesh, n, nocc, nemp, ng, prec):
     nk, g = int(np.prod(kmesh)), sphere(ng)
     return rp.rp_pair_density(ctx, ctypes.byref(cell(n, kmesh)), (I * 3)(0, 0, 0), nocc + nemp, 60, ptr(bands(nk, 60)),
-                              (I * 3)(2, 2, 2), big, big, 0, nocc, nocc, nocc + nemp, 0, nk, ng, ptr(g), prec, big)
+                              (I * 3)(8, 8, 8), big, big, 0, nocc, nocc, nocc + nemp, 0, nk, ng, ptr(g), prec, big)
 def problem(kmesh, n, nocc, nemp, ng, nfreq, kbatch, keep):
     nk, g, w, f = int(np.prod(kmesh)), sphere(ng), bands(int(np.prod(kmesh)), 60), np.linspace(0.0, 9.0, nfreq) + 0j
     keep += [g, w, f]
-    return Problem(cell(n, kmesh), (I * 3)(0, 0, 0), nocc + nemp, 60, ptr(w), (I * 3)(2, 2, 2), big, big, big, None, 0, nocc,
+    return Problem(cell(n, kmesh), (I * 3)(0, 0, 0), nocc + nemp, 60, ptr(w), (I * 3)(8, 8, 8), big, big, big, None, 0, nocc,
                    nocc, nocc + nemp, 0, nk, ng, ptr(g), nfreq, ptr(f), 0.1, 1, kbatch, 0, big)
 def screen(ng, nfreq):
     return rp.rp_screen_W(ctx, ctypes.byref(cell(16, (1, 1, 1))), (I * 3)(0, 0, 0), ng, ptr(sphere(ng)), nfreq, big, big, None)
@@ -213,3 +213,37 @@ def test_fp64_partial_sums_take_what_there_is(stand_in):
     assert [x["nslice"] for x in _chi(none)] == [1]
     assert [x["nslice"] for x in _chi(again)] == [1]        # nothing more is asked for
     assert no["status"] == 5 and not no["launches"]         # RP_E_NOMEM: no room for the weights
+
+
+def _ugrids(call, bands, nk, one):
+    assert call["status"] == 0 and call["err"] == ""
+    u = [x for x in call["launches"] if x["k"] == "ugrid"]
+    assert sum(x["n"] for x in u) == nk
+    for x in u:
+        assert x["bands"] == bands and x["n"] * one <= x["room"]
+    return u
+
+
+def test_u_grids_of_fewer_k_points(stand_in):
+    """27 k-points of 12 bands on 20^3 in FP64: 1.5 MB of u-grids each, taken
+    together where there is room, fewer at a time where there is not; one
+    k-point's are the least.  The same in a batch, whose graphs hold the
+    groups that the workspace had room for."""
+    one = 16 * 12 * 20 ** 3      # the batch: M 0.8 MB, weights and partial sums beside it
+    new = "rp.rp_destroy(ctx); rp.rp_create(ctypes.byref(ctx), 0, None); "
+    full, some, least, no, batch, again, run = stand_in(
+        "call(400*MB, pair, (3, 3, 3), 20, 4, 8, 60, 0)\n" +
+        new + "call(12*MB, pair, (3, 3, 3), 20, 4, 8, 60, 0)\n" +
+        new + "call(2*MB, pair, (3, 3, 3), 20, 4, 8, 60, 0)\n" +
+        new + "call(1*MB, pair, (3, 3, 3), 20, 4, 8, 60, 0)\n" +
+        new + "keep = []; p = problem((3, 3, 3), 20, 4, 8, 60, 20, 27, keep)\n"
+        "call(16*MB, rp.rp_chi0_batch, ctx, 1, ctypes.byref(p), 0); call(0, rp.rp_chi0_batch, ctx, 1, ctypes.byref(p), 0)\n" +
+        # M of 21 MB and its weights have to fit beside the grids, which were asked for first
+        new + "p = problem((3, 3, 3), 20, 16, 32, 100, 20, 27, keep); call(40*MB, rp.rp_chi0_run, ctx, ctypes.byref(p), 0)\n")
+    assert len(_ugrids(full, 12, 27, one)) == 1
+    assert 1 < len(_ugrids(some, 12, 27, one)) < 27
+    assert len(_ugrids(least, 12, 27, one)) == 27
+    assert no["status"] == 5 and not no["launches"]
+    assert 1 < len(_ugrids(batch, 12, 27, one)) < 27
+    assert [x["k"] for x in again["launches"]] == ["graph"]
+    assert 1 < len(_ugrids(run, 48, 27, 4 * one)) <= 27
