@@ -1195,12 +1195,12 @@ rp_status rp_screen_W(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int ng,
     if ((st = upload(ctx, ctx->glist, gsph, sizeof(int) * 3 * ng)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->vsqrt, sizeof(double) * ng)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->piv, sizeof(int) * (size_t)ng * nfreq)) != RP_OK) return st;
-    if ((st = ensure(ctx, ctx->rho, invert_scratch_bytes(ng, nfreq))) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->rho, invert_scratch_bytes(ng, nfreq), invert_scratch_bytes(ng, 1))) != RP_OK) return st;
     double *vs = (double *)ctx->vsqrt.p;
     StageTimer t(ctx, RP_STAGE_SCREEN);
     launch_vsqrt(ctx->stream, g, ng, (const int *)ctx->glist.p, vs, ctx->flag);
     launch_eps(ctx->stream, nfreq, ng, vs, (const double2 *)chi, a, ctx->flag);
-    launch_invert(ctx->stream, nfreq, ng, a, (double2 *)ctx->rho.p, (int *)ctx->piv.p, ctx->flag);
+    launch_invert(ctx->stream, nfreq, ng, a, (double2 *)ctx->rho.p, ctx->rho.bytes, (int *)ctx->piv.p, ctx->flag);
     if (W) launch_W(ctx->stream, nfreq, ng, vs, a, (double2 *)W);
     return check_launch(ctx, "screen");
 }
@@ -1306,7 +1306,7 @@ rp_status rp_screen_head(rp_ctx *ctx, const rp_cell *cell, int ng, const int *gs
     if ((st = upload(ctx, ctx->freq, freq_eV, sizeof(double2) * nfreq)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->vsqrt, sizeof(double) * ng)) != RP_OK) return st;
     if ((st = ensure(ctx, ctx->piv, sizeof(int) * (size_t)ng * nfreq)) != RP_OK) return st;
-    if ((st = ensure(ctx, ctx->rho, invert_scratch_bytes(ng, nfreq))) != RP_OK) return st;
+    if ((st = ensure_some(ctx, ctx->rho, invert_scratch_bytes(ng, nfreq), invert_scratch_bytes(ng, 1))) != RP_OK) return st;
     double *vs = (double *)ctx->vsqrt.p;
     StageTimer t(ctx, RP_STAGE_SCREEN);
     launch_vsqrt(ctx->stream, g, ng, (const int *)ctx->glist.p, vs, ctx->flag, true);
@@ -1314,7 +1314,7 @@ rp_status rp_screen_head(rp_ctx *ctx, const rp_cell *cell, int ng, const int *gs
     const double2 *fq = (const double2 *)ctx->freq.p;
     const bool drude = ctx->drude_wq != 0.0;
     if (drude) launch_drude_head(ctx->stream, nfreq, ng, fq, ctx->drude_wq, ctx->drude_delta, a);
-    launch_invert(ctx->stream, nfreq, ng, a, (double2 *)ctx->rho.p, (int *)ctx->piv.p, ctx->flag);
+    launch_invert(ctx->stream, nfreq, ng, a, (double2 *)ctx->rho.p, ctx->rho.bytes, (int *)ctx->piv.p, ctx->flag);
     if (drude) launch_drude_zero(ctx->stream, nfreq, ng, fq, ctx->drude_delta, a);
     if (optics) launch_optics(ctx->stream, nfreq, ng, a, fq, optics);
     return check_launch(ctx, "screen head");

@@ -253,7 +253,9 @@ void launch_vsqrt(hipStream_t s, const Geometry &g, int ng, const int *gsph, dou
 void launch_eps(hipStream_t s, int nfreq, int ng, const double *vs, const double2 *chi,
                 double2 *eps, int *flag);
 size_t invert_scratch_bytes(int ng, int nfreq);
-void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, int *piv, int *flag);
+// as many matrices at a time as scratch holds (at least one)
+void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, size_t scratch_bytes, int *piv,
+                   int *flag);
 void launch_W(hipStream_t s, int nfreq, int ng, const double *vs, const double2 *einv,
               double2 *W);
 

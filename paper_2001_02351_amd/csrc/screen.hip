@@ -623,7 +623,8 @@ static void panel_steps(hipStream_t s, int nfreq, int ng, int c0, int nb, double
     }
 }
 
-void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, int *piv, int *flag)
+// the panels of nfreq matrices (see launch_invert)
+static void invert_steps(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, int *piv, int *flag)
 {
     const unsigned t = (unsigned)((ng + 63) / 64);
     const size_t panel = (size_t)kGjNb * ng * nfreq;
@@ -652,6 +653,14 @@ void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratc
                            pbn, rk);
         std::swap(pb, pbn);
     }
+}
+
+void launch_invert(hipStream_t s, int nfreq, int ng, double2 *a, double2 *scratch, size_t scratch_bytes, int *piv,
+                   int *flag)
+{
+    const int per = (int)std::min<size_t>(nfreq, scratch_bytes / invert_scratch_bytes(ng, 1));
+    for (int f = 0; f < nfreq; f += per)
+        invert_steps(s, std::min(per, nfreq - f), ng, a + (long)f * ng * ng, scratch, piv + (long)f * ng, flag);
     const long rows = (long)nfreq * ng;
     hipLaunchKernelGGL(k_gj_unswap, dim3((unsigned)((rows + 127) / 128)), dim3(128), 0, s, nfreq, ng, a,
                        piv);

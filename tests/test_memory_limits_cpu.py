@@ -247,3 +247,19 @@ def test_u_grids_of_fewer_k_points(stand_in):
     assert 1 < len(_ugrids(batch, 12, 27, one)) < 27
     assert [x["k"] for x in again["launches"]] == ["graph"]
     assert 1 < len(_ugrids(run, 48, 27, 4 * one)) <= 27
+
+
+def test_inversion_of_fewer_matrices(stand_in):
+    """16 matrices of 300: 0.94 MB of panels and pivot rows each, all at once
+    where there is room, fewer at a time where there is not."""
+    one = 16 * 64 * (3 * 300 + 16)
+    new = "rp.rp_destroy(ctx); rp.rp_create(ctypes.byref(ctx), 0, None); "
+    full, some, least, no = stand_in("call(40*MB, screen, 300, 16)\n" + new + "call(5*MB, screen, 300, 16)\n" + new +
+                                     "call(1*MB, screen, 300, 16)\n" + new + "call(MB//2, screen, 300, 16)\n")
+    for call, groups in ((full, 1), (some, None), (least, 16)):
+        assert call["status"] == 0 and call["err"] == ""
+        gj = [x for x in call["launches"] if x["k"] == "gj"]
+        assert sum(x["nmat"] for x in gj) == 16
+        assert all(x["nmat"] * one <= x["room"] for x in gj)
+        assert len(gj) == groups if groups else 1 < len(gj) < 16
+    assert no["status"] == 5 and not no["launches"]
