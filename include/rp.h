@@ -190,7 +190,10 @@ rp_status rp_weights(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nban
  * for the pairs of one rp_pair_density call (same ranges, same M layout).
  * prec selects the contraction: RP_FP64 (FP64 matrix cores), RP_SPLIT_BF16
  * or RP_SPLIT_BF16_X6 (BF16 split products with FP32 accumulation, added into
- * chi in FP64).  Weights are always FP64.
+ * chi in FP64).  Weights are always FP64.  The split forms take each
+ * tetrahedron's integral by itself at complex frequencies, where rp_weights
+ * and RP_FP64 sum a moment series for distant ones: the two agree to about
+ * 1e-11 of a weight.
  *
  * M          (dev)   : c128[npair][ng] from rp_pair_density
  * accumulate         : 0 overwrite chi, 1 add into chi

@@ -684,7 +684,7 @@ void launch_weights(hipStream_t s, const int kmesh[3], const int iq[3], int nban
                            freq_eV, delta_eV, w);
         return;
     }
-    // the split forms at complex frequencies: the same bits as ever (weights_direct.hip)
+    // the split forms at complex frequencies: every difference by itself (weights_direct.hip says why)
     if (direct && mode == RP_W_TETRA_METAL) {
         launch_weights_direct(s, kmesh, iq, nband, E_eV, T, o0, o1, e0, e1, k0, k1, nfreq, freq_eV, delta_eV,
                               ef_eV / kHartreeEv, w);

@@ -7,11 +7,12 @@
 // their size (the three-term form: 4e-8, where few pairs make up chi).  The
 // moment series of tetra.hip is the more accurate (1e-16 against up to 1e-13
 // here) and the faster (14 112 pairs x 10 frequencies: 0.86 against 7.45 ms),
-// but its weights change about ten such roundings of 5 million; with this
+// but its weights change about one such rounding in a million (67 of 63
+// million, six spectra of three widths, insulating and metallic); with this
 // kernel chi stays the same in every bit.  Insulators have k_weights without
-// its series for this, which has the same bits; a cut tetrahedron's pieces are
-// summed there in another order.  Real weights (imaginary axis) and FP64 take
-// the series.
+// its series for this, which has the same bits.  Real weights (imaginary axis)
+// take the series: none of 32 million of their roundings changes.  FP64 takes
+// it everywhere.
 #include "tetra_dd.h"
 
 namespace rp {
@@ -72,8 +73,8 @@ constexpr int kDThreads = 128;
 // One thread per (pair, frequency).  The corner energies e_j of the 15
 // distinct corners live in registers (the tetrahedron table indexes them with
 // the same slot in every lane, which the compiler turns into register-relative
-// moves) and the logarithms log(z - e_j) in LDS ([slot][thread]), so five
-// 128-thread blocks share a CU; each of the 24 tetrahedra sorts its five nodes
+// moves) and the logarithms log(z - e_j) in LDS ([slot][thread]) with the two
+// bands' corner energies: 60 KB per 128-thread block, two blocks per CU; each of the 24 tetrahedra sorts its five nodes
 // (four corners, k's corner doubled) together with their logarithms and
 // evaluates I_v(z) and I_v(z') (only I_v(z) when z' = z*).
 //
@@ -81,7 +82,7 @@ constexpr int kDThreads = 128;
 // all four corners of a tetrahedron and E_a > ef at all four, the insulating
 // integral applies; with E_b >= ef or E_a <= ef at all four, the tetrahedron
 // contributes nothing; otherwise clipped_vertex_integral tiles the part where
-// E_b < ef < E_a (the corner energies of both bands are kept in LDS too).
+// E_b < ef < E_a.
 __global__ void __launch_bounds__(kDThreads)
 k_weights_direct(int K1, int K2, int K3, int q1, int q2, int q3, int nband, const double *E, const double *T, int o0,
                  int nO, int e0, int nE, int k0, long npair, int nfreq, const double2 *freq, double delta, double ef,
