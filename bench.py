@@ -923,9 +923,9 @@ def main():
         t_ugrid = split["stage_ms_per_step"]["ugrid"] / d.nk / 1e3
         alg = (prob.nocc + prob.nemp) * int(np.prod(pair_grid)) * 8 + prob.nocc * prob.nemp * d.ng * 16
         hbm = {
-            "pair_kernel": {"bytes_per_launch": pc["pair_bytes_per_launch"], "ms_per_launch": t_pair * 1e3,
+            "pair_kernel": {"bytes_per_k": pc["pair_bytes_per_launch"], "ms_per_k": t_pair * 1e3,
                             "achieved_GB_s": pc["pair_bytes_per_launch"] / t_pair / 1e9,
-                            "algorithmic_bytes_per_launch": alg,
+                            "algorithmic_bytes_per_k": alg,
                             "algorithmic_GB_s": alg / t_pair / 1e9, "peak_GB_s": PEAK_HBM_GBS},
             "ugrid_kernels": {"bytes_per_k": pc["ugrid_bytes_per_k"], "ms_per_k": t_ugrid * 1e3,
                               "achieved_GB_s": pc["ugrid_bytes_per_k"] / t_ugrid / 1e9,

@@ -140,6 +140,8 @@ const char *rp_last_error(const rp_ctx *ctx);
  *                      split modes in FP32 (M then carries ~1e-7 relative
  *                      error, far below what the split contraction keeps)
  * M        (dev)     : c128[k1-k0][e1-e0][o1-o0][ng] output
+ * Device workspace: the u-grids of as many k-points (up to 32) as fit 150 MB or
+ * what the device has left, at least one.
  * Errors: RP_E_NULL, RP_E_SHAPE, RP_E_RANGE, RP_E_ALIAS, RP_E_UNSUPPORTED,
  * RP_E_NOMEM, RP_E_DEVICE.
  */
@@ -198,6 +200,10 @@ rp_status rp_weights(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nban
  * M          (dev)   : c128[npair][ng] from rp_pair_density
  * accumulate         : 0 overwrite chi, 1 add into chi
  * chi        (dev)   : c128[nfreq][ng][ng], hartree^-1
+ * Device workspace: the weights, c128[nfreq][npair]; split forms the operands
+ * and partial tiles; RP_FP64 up to 256 MiB of partial sums, or what the device
+ * has left (fewer frequencies at a time then; where not even one frequency's
+ * fit, chi is summed in another grouping).
  * Errors: as rp_weights.
  */
 rp_status rp_chi0_accumulate(rp_ctx *ctx, const rp_cell *cell, const int iq[3], int nband,
@@ -329,6 +335,9 @@ rp_status rp_chi0_run(rp_ctx *ctx, const rp_problem *p, rp_precision prec);
  * chi     (dev)   : c128[nfreq][ng][ng]
  * eps_inv (dev)   : c128[nfreq][ng][ng] output, or NULL
  * W       (dev)   : c128[nfreq][ng][ng] output in eV, or NULL
+ * Device workspace: about 3 KB per matrix row (64 (3 ng + 16) complex values a
+ * matrix, for as many of the nfreq matrices as the device has room for, at least
+ * one), and c128[nfreq][ng][ng] where eps_inv is NULL.
  * A pivot of magnitude below 1e-13 (eps is dimensionless with a unit-scale
  * diagonal, so this means a condition number beyond ~1e13) is reported by
  * rp_synchronize as RP_E_SINGULAR; a non-finite value as RP_E_RANGE.

@@ -22,9 +22,10 @@
 // mean of 1/|q|^2 over the q-cell around Gamma; the wings are dropped (odd
 // in q to leading order).
 //
-// The quadratic forms run as T = eps^-1 conj(P)^T on the FP64 matrix cores
-// (64 x 64 tiles of (G, vector), 16x16x4 FP64 MFMAs), then per vector or per
-// orbital pair a reduction with the densities themselves.
+// The exchange quadratic forms run as T = eps^-1 conj(P)^T on the FP64 matrix
+// cores (k_wquad: 64 rows G x 80 or 32 densities per workgroup), each tile
+// reduced against P in place; those of the orbital pairs are k_wbody's
+// (wannier.hip), the densities k_density's (density.hip) on the edges it takes.
 #include <type_traits>
 
 #include "fft_lds.h"

@@ -50,8 +50,8 @@ __global__ void k_unfold_phase(int ng, const int *__restrict__ gsph, double t0, 
 // chunk, f), the source indices staged in LDS (4 ng bytes), the phases read
 // through the cache.  STAGED: the source row passes through LDS, read in order
 // and picked there; picked from memory, 16 bytes of each line at a time, an
-// operation that shuffles the list (20 frequencies, N_G = 1500) took 392 us
-// instead of 253 (5.7 TB/s).  Which of the two: launch_unfold_matrix.
+// operation that shuffles the list (20 frequencies, N_G = 1500) took 483 us
+// instead of 302 (4.8 TB/s).  Which of the two: launch_unfold_matrix.
 template <bool STAGED>
 __global__ void __launch_bounds__(256) k_unfold_matrix(int ng, int ng_src, const int *__restrict__ idx,
                                                        const double2 *__restrict__ ph, const double2 *__restrict__ src,
@@ -99,10 +99,11 @@ void launch_unfold_matrix(hipStream_t s, int nfreq, int ng, int ng_src, const in
     const dim3 grid((unsigned)((ng + 3) / 4), (unsigned)nfreq);
     // Rows through LDS where most of a row is picked and two workgroups share a
     // CU.  Staging reads the whole row; picking reads the lines that the target
-    // needs.  Staged against picked, equal lists: 300 27.8/28.0 us, 1000
-    // 246/356, 2500 321/439, 4000 339/413, above two workgroups 4500 317/290,
-    // 6000 532/522; targets of 3/4 of the source: 300 22/17, 1000 170/196, 3000
-    // 269/254; of 1/2: 1000 105/85, 4000 123/82; of 1/20: 4000 22/9, 8000 44/11.
+    // needs.  Staged/picked in us (0.6 GB of source matrices, at most 40 of them),
+    // equal lists: 300 27.8/28.0, 1000 246/356, 2500 321/439, 4000
+    // 339/413, above two workgroups 4500 317/290, 6000 532/522; targets of 3/4 of
+    // the source: 300 22/17, 1000 170/196, 3000 269/254; of 1/2: 1000 105/85, 4000
+    // 123/82; of 1/20: 4000 22/9, 8000 44/11.
     const size_t lds = sizeof(double2) * (size_t)ng_src + sizeof(int) * (size_t)ng;
     if (ng_src >= 512 && 5L * ng >= 4L * ng_src && lds <= 80 * 1024) {
         if (lds > 65536)
