@@ -62,7 +62,8 @@ __global__ void k_wgather(int nwan, int N1, int N2, int N3, int nlist, const int
     }
 }
 
-constexpr int kBodyRows = 32;   // rows of eps^-1 per workgroup of k_wbody
+// rows of eps^-1 per workgroup of k_wbody: what the registers hold beside 16 or 32 orbitals
+int body_rows(int nwan) { return nwan <= 16 ? 32 : 16; }
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
@@ -71,14 +72,32 @@ __device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
 }
 
+// s + e becomes s + e + x, e the rounding errors of s (not a number where s is infinite)
+template <typename T> __device__ __forceinline__ void add_kept(T &s, T &e, T x)
+{
+    const T t = s + x, b = t - s;
+    e += (s - (t - b)) + (x - b);
+    s = t;
+}
+
+__device__ __forceinline__ double kept(double s, double e) { return isfinite(e) ? s + e : s; }
+
 // Quadratic forms of all orbital pairs: over the rows of one workgroup,
 //   part[f][row block][i][j] = sum_G P[i][G] sum_G' eps^-1[f][G][G'] conj(P[j][G'])
-// with G, G' in [klo, ng).  Bound by reading eps^-1 once.  A workgroup owns 32
-// rows G, each of its four waves a quarter of the columns G', so that enough
-// loads are in flight: the four lanes of a row read 64 contiguous bytes of it
-// (and of their orbital) straight into a matrix operand; 16 NC orbitals.  The product with P over the rows follows in LDS.
+// with G, G' in [klo, ng).  Bound by reading eps^-1 once.  A workgroup owns 16 RB
+// rows G (32, or 16 beside 32 orbitals), each of its four waves a quarter of the
+// columns G', so that enough loads are in flight: the four lanes of a row read
+// 64 contiguous bytes of it (and of their orbital) straight into a matrix
+// operand; 16 NC orbitals.  The product with P over the rows follows in LDS.
 // 20 x 1500^2, ten orbitals: 0.62 ms with one workgroup per row and a reduction
 // through LDS per orbital, 0.20 here (3.6 TB/s).
+//
+// A column quarter in one accumulator is a chain of hundreds of additions: W_ij
+// of 777 to 1200 vectors was off by 9e-16, against 3.5e-16 for sums by halves.
+// So the products of 16 columns start from zero, four columns each, are added
+// by halves and join the total with its rounding errors kept, as do the rows:
+// 3.3e-16.  That costs no time up to 16 orbitals (ten: 306 us a call either
+// way), 10% above (20 x 1500^2, 32 orbitals: 479 -> 517 us, the rows halved).
 template <int NC, int RB>
 __global__ void __launch_bounds__(256, 2)
 k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, const double2 *__restrict__ einv,
@@ -96,14 +115,12 @@ k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, cons
     for (int rb = 0; rb < RB; rb++) row[rb] = E + (long)min(r0 + rb * 16 + li, ng - 1) * ng;
 #pragma unroll
     for (int c = 0; c < NC; c++) orb[c] = P + (long)min(c * 16 + li, nwan - 1) * ldp;
-    d4 accR[RB][NC], accI[RB][NC];
+    d4 accR[RB][NC], accI[RB][NC], errR[RB][NC], errI[RB][NC];
 #pragma unroll
     for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-        for (int c = 0; c < NC; c++) {
-            accR[rb][c] = d4{0.0, 0.0, 0.0, 0.0};
-            accI[rb][c] = d4{0.0, 0.0, 0.0, 0.0};
-        }
+        for (int c = 0; c < NC; c++)
+            accR[rb][c] = accI[rb][c] = errR[rb][c] = errI[rb][c] = d4{0.0, 0.0, 0.0, 0.0};
     double2 e[RB][4], o[NC][4];
     auto load = [&](int st) {
 #pragma unroll
@@ -135,22 +152,24 @@ k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, cons
         }
         if (st + 1 < s1) load(st + 1);
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
+        for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-            for (int rb = 0; rb < RB; rb++)
+            for (int c = 0; c < NC; c++) {
+                d4 pR[4], pI[4];
 #pragma unroll
-                for (int c = 0; c < NC; c++) {
-                    accR[rb][c] = mfma64(x[rb][q].x, y[c][q].x, accR[rb][c]);
-                    accI[rb][c] = mfma64(x[rb][q].y, y[c][q].x, accI[rb][c]);
+                for (int q = 0; q < 4; q++) {
+                    pR[q] = mfma64(x[rb][q].x, y[c][q].x, d4{0.0, 0.0, 0.0, 0.0});
+                    pI[q] = mfma64(x[rb][q].y, y[c][q].x, d4{0.0, 0.0, 0.0, 0.0});
                 }
 #pragma unroll
-            for (int rb = 0; rb < RB; rb++)
-#pragma unroll
-                for (int c = 0; c < NC; c++) {
-                    accR[rb][c] = mfma64(x[rb][q].y, y[c][q].y, accR[rb][c]);
-                    accI[rb][c] = mfma64(-x[rb][q].x, y[c][q].y, accI[rb][c]);
+                for (int q = 0; q < 4; q++) {
+                    pR[q] = mfma64(x[rb][q].y, y[c][q].y, pR[q]);
+                    pI[q] = mfma64(-x[rb][q].x, y[c][q].y, pI[q]);
                 }
-        }
+                const d4 sR = (pR[0] + pR[1]) + (pR[2] + pR[3]), sI = (pI[0] + pI[1]) + (pI[2] + pI[3]);
+                add_kept(accR[rb][c], errR[rb][c], sR);
+                add_kept(accI[rb][c], errI[rb][c], sI);
+            }
     }
     // result register r of lane (li, lk) holds row lk + 4 r, column li of a 16x16 block
 #pragma unroll
@@ -159,7 +178,7 @@ k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, cons
         for (int c = 0; c < NC; c++)
 #pragma unroll
             for (int r = 0; r < 4; r++)
-                sT[wave][rb * 16 + lk + 4 * r][c * 16 + li] = make_double2(accR[rb][c][r], accI[rb][c][r]);
+                sT[wave][rb * 16 + lk + 4 * r][c * 16 + li] = make_double2(kept(accR[rb][c][r], errR[rb][c][r]), kept(accI[rb][c][r], errI[rb][c][r]));
     __syncthreads();
     for (int t = tid; t < 256 * RB * NC; t += 256) {
         const int r = t / (16 * NC), c = t % (16 * NC);
@@ -168,12 +187,15 @@ k_wbody(int nwan, int ng, int klo, const double2 *__restrict__ P, long ldp, cons
     __syncthreads();
     for (int t = tid; t < nwan * nwan; t += 256) {
         const int i = t / nwan, j = t - i * nwan;
-        double2 s = make_double2(0.0, 0.0);
+        double2 s = make_double2(0.0, 0.0), d = s;
         for (int r = 0; r < 16 * RB; r++) {
             const int G = r0 + r;
-            if (G >= klo && G < ng) s = cadd(s, cmul(P[(long)i * ldp + G], sT[0][r][j]));
+            if (G < klo || G >= ng) continue;
+            const double2 v = cmul(P[(long)i * ldp + G], sT[0][r][j]);
+            add_kept(s.x, d.x, v.x);
+            add_kept(s.y, d.y, v.y);
         }
-        part[((long)f * gridDim.x + blockIdx.x) * nwan * nwan + t] = s;
+        part[((long)f * gridDim.x + blockIdx.x) * nwan * nwan + t] = make_double2(kept(s.x, d.x), kept(s.y, d.y));
     }
 }
 
@@ -222,14 +244,18 @@ void launch_wannier_gather(hipStream_t s, const Geometry &g, int nwan, int nlist
                        (int)zero_ok);
 }
 
-size_t wbody_part(int nfreq, int nwan, int ng) { return (size_t)nfreq * ((ng + kBodyRows - 1) / kBodyRows) * nwan * nwan; }
+size_t wbody_part(int nfreq, int nwan, int ng)
+{
+    return (size_t)nfreq * ((ng + body_rows(nwan) - 1) / body_rows(nwan)) * nwan * nwan;
+}
 
 void launch_wbody(hipStream_t s, int nfreq, int nwan, int ng, int klo, const double2 *P, long ldp, const double2 *einv,
                   const double2 *tail, double pre, double2 *part, double2 *out)
 {
-    const dim3 grid((unsigned)((ng + kBodyRows - 1) / kBodyRows), (unsigned)nfreq);
-    if (nwan <= 16) hipLaunchKernelGGL((k_wbody<1, kBodyRows / 16>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
-    else hipLaunchKernelGGL((k_wbody<2, kBodyRows / 16>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
+    const int rows = body_rows(nwan);
+    const dim3 grid((unsigned)((ng + rows - 1) / rows), (unsigned)nfreq);
+    if (nwan <= 16) hipLaunchKernelGGL((k_wbody<1, 2>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
+    else hipLaunchKernelGGL((k_wbody<2, 1>), grid, dim3(256), 0, s, nwan, ng, klo, P, ldp, einv, part);
     const long n = (long)nwan * nwan * nfreq;
     hipLaunchKernelGGL(k_wbody_sum, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, nwan * nwan, nfreq, (int)grid.x,
                        part, tail, pre, out);
