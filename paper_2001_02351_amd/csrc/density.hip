@@ -14,7 +14,10 @@
 // a few densities spread their planes over several workgroups each)
 // walks the grid two or four planes p1 at a time: each quad of lanes transforms a row along axis 3,
 // keeping the list's m3 window in LDS, then the window's columns along axis 2;
-// the list's vectors, a few per thread, add their axis-1 phase in registers.
+// the list's vectors, a few per thread, add their axis-1 phase in registers: a
+// group's planes from zero, then the group's sum to the total, up to five
+// vectors per thread with its rounding errors kept (one addition per plane put
+// V and X 4.4e-16 off on 256 x 16 x 16, 1.9e-16 through whole grids and here).
 // Planes and rows outside the cut are skipped.  Bound by FP64 arithmetic and
 // LDS.  Through whole grids in memory (overlap grids written, three transform
 // passes, a gather) the 2700 exchange densities of the 48^3 workload's 27 cells
@@ -58,9 +61,16 @@ __global__ void __launch_bounds__(256) k_density_sum(DensityArgs d, int nv, int 
     if (t >= n) return;
     const long v = t / d.nlist;
     const int gi = (int)(t - v * d.nlist);
-    double2 s = d.part[t];
-    for (int z = 1; z < nz; z++) s = cadd(s, d.part[z * n + t]);
-    d.P[v * d.ldp + gi] = cscale(s, density_scale(d, gi));
+    double2 s = make_double2(0.0, 0.0), e = s;
+    for (int z0 = 0; z0 < nz; z0 += 4) {
+        double2 x[4];
+#pragma unroll
+        for (int z = 0; z < 4; z++) x[z] = z0 + z < nz ? d.part[(z0 + z) * n + t] : make_double2(0.0, 0.0);
+        const double2 y = cadd(cadd(x[0], x[1]), cadd(x[2], x[3]));
+        add_kept(s.x, e.x, y.x);
+        add_kept(s.y, e.y, y.y);
+    }
+    d.P[v * d.ldp + gi] = cscale(make_double2(kept(s.x, e.x), kept(s.y, e.y)), density_scale(d, gi));
 }
 
 __device__ __forceinline__ void lds_sync()
@@ -103,7 +113,9 @@ __global__ void __launch_bounds__(NT, 512 / NT) k_density(DensityArgs d)
         sincospi(2.0 * d.q[a] * rt, &sn, &cs);
         (a == 0 ? c1 : (a == 1 ? c2 : c3))[p] = in ? make_double2(cs, sn) : make_double2(0.0, 0.0);
     }
-    double2 acc[MAXG];
+    // the sums of up to five vectors per thread keep their rounding errors
+    constexpr bool KEPT = MAXG <= 5;
+    double2 acc[MAXG], err[KEPT ? MAXG : 1];
     // per vector: bits 0-13 the window index, 14-21 m1 mod N1
     unsigned pk[MAXG];
     const int gbase = blockIdx.y * NT * MAXG + tid;
@@ -111,6 +123,7 @@ __global__ void __launch_bounds__(NT, 512 / NT) k_density(DensityArgs d)
     for (int t = 0; t < MAXG; t++) {
         const int gi = gbase + t * NT;
         acc[t] = make_double2(0.0, 0.0);
+        if constexpr (KEPT) err[t] = make_double2(0.0, 0.0);
         pk[t] = 0;
         if (gi < d.nlist) {
             const int *m = d.g + 3 * gi;
@@ -172,16 +185,38 @@ __global__ void __launch_bounds__(NT, 512 / NT) k_density(DensityArgs d)
             for (int k = 0; k < Q; k++) col[(4 * k + res) * L3] = y[k];
         }
         lds_sync();
-        for (int pl = 0; pl < npl; pl++) {
-            const unsigned p1 = (unsigned)act[a + pl];
-            const double2 *w = win_dyn + pl * wsize;
+        // TB vectors at a time (all 13 at once, or one after the other, spill or wait: 1.1 times
+        // the time of a long list)
+        constexpr int TB = MAXG <= 5 ? MAXG : 7;
 #pragma unroll
-            for (int t = 0; t < MAXG; t++) {
-                const unsigned u = pk[t], st = (u >> 14) * p1;
-                const double2 e = tw1[N1 > 1 ? st - __umulhi(st, magic) * N1 : 0];
-                const double2 v = w[u & 0x3fffu];
-                acc[t].x += v.x * e.x - v.y * e.y;
-                acc[t].y += v.x * e.y + v.y * e.x;
+        for (int t0 = 0; t0 < MAXG; t0 += TB) {
+            double2 z[TB];
+#pragma unroll
+            for (int t = 0; t < TB; t++) z[t] = make_double2(0.0, 0.0);
+#pragma unroll 1
+            for (int pl = 0; pl < npl; pl++) {
+                const unsigned p1 = (unsigned)act[a + pl];
+                const double2 *w = win_dyn + pl * wsize;
+#pragma unroll
+                for (int t = 0; t < TB; t++) {
+                    if (t0 + t >= MAXG) break;
+                    const unsigned u = pk[t0 + t], st = (u >> 14) * p1;
+                    const double2 e = tw1[N1 > 1 ? st - __umulhi(st, magic) * N1 : 0];
+                    const double2 v = w[u & 0x3fffu];
+                    z[t].x += v.x * e.x - v.y * e.y;
+                    z[t].y += v.x * e.y + v.y * e.x;
+                }
+            }
+#pragma unroll
+            for (int t = 0; t < TB; t++) {
+                if (t0 + t >= MAXG) break;
+                double2 &s = acc[t0 + t];
+                if constexpr (KEPT) {
+                    add_kept(s.x, err[t0 + t].x, z[t].x);
+                    add_kept(s.y, err[t0 + t].y, z[t].y);
+                } else {
+                    s = cadd(s, z[t]);
+                }
             }
         }
         lds_sync();
@@ -190,6 +225,7 @@ __global__ void __launch_bounds__(NT, 512 / NT) k_density(DensityArgs d)
     for (int t = 0; t < MAXG; t++) {
         const int gi = gbase + t * NT;
         if (gi >= d.nlist) continue;
+        if constexpr (KEPT) acc[t] = make_double2(kept(acc[t].x, err[t].x), kept(acc[t].y, err[t].y));
         if (d.part) d.part[((long)blockIdx.z * gridDim.x + blockIdx.x) * d.nlist + gi] = acc[t];
         else d.P[(long)blockIdx.x * d.ldp + gi] = cscale(acc[t], density_scale(d, gi));
     }
@@ -199,11 +235,16 @@ __global__ void __launch_bounds__(NT, 512 / NT) k_density(DensityArgs d)
 
 }  // namespace
 
+// Vectors of the list per thread: 4 or 5, whose sums keep their rounding errors,
+// or 13 (the registers) for a longer list on up to 64 planes, sixteen groups of
+// them; a list longer than the threads hold takes several workgroups per density.
+static int vectors_per_thread(int N1, int nlist) { return nlist <= 1024 ? 4 : nlist <= 2560 || N1 > 64 ? 5 : 13; }
+
 // workgroups that share a density's planes: enough for one workgroup per CU,
 // each with four planes at least
 static int density_split(int N1, int nv, int nlist)
 {
-    const int chunks = (nlist + 6655) / 6656;
+    const int per = 512 * vectors_per_thread(N1, nlist), chunks = (nlist + per - 1) / per;
     return std::max(1, std::min(N1 / 4, 256 / std::max(1, nv * chunks)));
 }
 
@@ -254,8 +295,7 @@ void launch_density(hipStream_t s, const Geometry &g, int nwan, const double *ph
     const int nz = density_split(g.fft[0], nv, nlist);
     d.part = nz > 1 ? part : nullptr;
     d.flag = flag;
-    // vectors per thread: the list's, up to 13 (the registers); a longer list
-    // takes several workgroups per density
+    const int per = vectors_per_thread(g.fft[0], nlist);
     auto go = [&](auto kern, int per, int nt) {
         const size_t shm = sizeof(double2) * (size_t)(nt / 128) * N * d.L3;
         if (shm > 32768)
@@ -266,8 +306,8 @@ void launch_density(hipStream_t s, const Geometry &g, int nwan, const double *ph
     switch (N) {
 #define RP_CASE(e)                                                                                        \
     case e:                                                                                               \
-        if (nlist <= 1024) go(k_density<e, 4, 256>, 4, 256);                                              \
-        else if (nlist <= 2560) go(k_density<e, 5, 512>, 5, 512);                                         \
+        if (per == 4) go(k_density<e, 4, 256>, 4, 256);                                                   \
+        else if (per == 5) go(k_density<e, 5, 512>, 5, 512);                                              \
         else go(k_density<e, 13, 512>, 13, 512);                                                          \
         break;
         RP_DENSITY_LENGTHS(RP_CASE)

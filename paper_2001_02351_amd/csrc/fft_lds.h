@@ -47,6 +47,16 @@ template <typename C> __device__ __forceinline__ C cscale(C a, typename CxT<C>::
 }
 template <typename C> __device__ __forceinline__ C mul_i(C a) { return mkc<C>(-a.y, a.x); }
 
+// s + e becomes s + e + x, e the rounding errors of s (not a number where s is infinite)
+template <typename T> __device__ __forceinline__ void add_kept(T &s, T &e, T x)
+{
+    const T t = s + x, b = t - s;
+    e += (s - (t - b)) + (x - b);
+    s = t;
+}
+
+__device__ __forceinline__ double kept(double s, double e) { return isfinite(e) ? s + e : s; }
+
 // tw[t] = e^{+2 pi i t/n}, t < n (evaluated in FP64)
 template <typename C> __device__ __forceinline__ void fill_twiddles(C *tw, int n, int tid, int nth)
 {

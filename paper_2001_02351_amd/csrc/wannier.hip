@@ -72,16 +72,6 @@ __device__ __forceinline__ d4 mfma64(double x, double y, d4 c)
     return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
 }
 
-// s + e becomes s + e + x, e the rounding errors of s (not a number where s is infinite)
-template <typename T> __device__ __forceinline__ void add_kept(T &s, T &e, T x)
-{
-    const T t = s + x, b = t - s;
-    e += (s - (t - b)) + (x - b);
-    s = t;
-}
-
-__device__ __forceinline__ double kept(double s, double e) { return isfinite(e) ? s + e : s; }
-
 // Quadratic forms of all orbital pairs: over the rows of one workgroup,
 //   part[f][row block][i][j] = sum_G P[i][G] sum_G' eps^-1[f][G][G'] conj(P[j][G'])
 // with G, G' in [klo, ng).  Bound by reading eps^-1 once.  A workgroup owns 16 RB
